@@ -184,7 +184,8 @@ cp_status coverprune_fst_capacity(const void* feats, cp_dtype dtype, int64_t n, 
  *             c0 * max v < 2^(52 - S); costs are taken in [0, c0]) and summed
  *             exactly in 64-bit integers, so picks can differ from the dense
  *             sweep's float64 sums only between gains within rounding of
- *             each other.
+ *             each other.  Gains compare to 2^-31 relative
+ *             (below that the smaller index wins).
  *             For n <= 32768 every compute unit keeps all n best costs and
  *             finds the targets a pick improves itself, from the pick's row
  *             of a source-major copy of the cost that the first pass writes
@@ -194,12 +195,13 @@ cp_status coverprune_fst_capacity(const void* feats, cp_dtype dtype, int64_t n, 
  *             compute units, which read those targets' whole rows and
  *             exchange per-column sums through the workspace (8 bytes per
  *             column and compute unit, up to 2 KB per token).  For
- *             n <= 16384 and k > 128 the steps after the 128th run from
- *             per-candidate lists of the targets each candidate can still
- *             improve (4 KB per token in the workspace), with the next
- *             winner predicted without an exchange when bounds that every
- *             compute unit computes identically prove it; the same
- *             integers, so the same picks.  Larger scenes, or
+ *             n <= 16384 the steps after the first n / 128 (at least 8) run
+ *             from per-candidate lists of the targets each candidate can
+ *             still improve (4 KB per token in the workspace when k > 128, in
+ *             the copy's place otherwise), many picks per exchange: those
+ *             among the best candidates that bounds every compute unit
+ *             computes identically prove to come next; the same integers, so
+ *             the same picks.  Larger scenes, or
  *             CP_SGS_INCREMENTAL | CP_SGS_COMPACT, exchange the improved
  *             targets between the compute units instead (about 45 bytes
  *             per token, slower per step).  Both schedules sum the same
@@ -271,8 +273,7 @@ cp_status coverprune_prune(const void* feats, cp_dtype dtype, int64_t n, int64_t
  * cooperative launch: scene s gets its own group of blocks (one block per
  * compute unit in all, groups balanced by tokens per block) and its own
  * exchanges, so each scene's result is what coverprune_sgs_select with
- * CP_SGS_INCREMENTAL computes for it alone (its block partition can differ,
- * which matters only for gains equal to 2^-31 relative in different blocks).
+ * CP_SGS_INCREMENTAL computes for it alone.
  * The call takes as long as its slowest scene.
  *
  *   scenes    host array of `count` scene descriptions (read during the call

@@ -62,7 +62,6 @@ __device__ __forceinline__ void inc_body(const IncDev& a, int blk, int nb) {
   unsigned char* ssel = reinterpret_cast<unsigned char*>(sv + a.W);       // [W] chosen columns
   __shared__ long long red[kBlock];
   __shared__ long long sg[kWaves];
-  __shared__ int si[kWaves];
   __shared__ int swt[kWaves];
   __shared__ unsigned long long su[kWaves];
   __shared__ int spre[kMaxBlocks + 1];        // slice offsets
@@ -98,7 +97,7 @@ __device__ __forceinline__ void inc_body(const IncDev& a, int blk, int nb) {
     if (tid < kWaves) sLw[tid] = tid == 0 ? L0 : 0;
   }
 
-  publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), sg, si);
+  publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), su);
 
   for (int step = 0; step < a.k; ++step) {
     // Some block has a candidate while unchosen columns remain; the clamp
@@ -265,7 +264,7 @@ __device__ __forceinline__ void inc_body(const IncDev& a, int blk, int nb) {
     // 4. This block's candidate for the next step.
     if (step + 1 < a.k)
       publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, (step + 1) & 1, blk),
-                     epoch_of(step + 1), sg, si);
+                     epoch_of(step + 1), su);
   }
   __syncthreads();
   if (blk == 0 && tid == 0 && obj_step >= 0 && a.step_obj) {
@@ -345,34 +344,19 @@ __device__ __forceinline__ int fixed_scale(const IncDev& a, double* sd) {
 // outside the winner's block), a lower bound on its fixed-point gain (from
 // its key), and an upper bound U on every other candidate's truncated gain:
 // the best keys of all blocks but the winner's and r's, and the second-best
-// keys of those two (a block's other columns gain at most its second best,
-// and gains only fall).  While applying the step's hits every block also sums
+// keys of those two (a block's other columns are at most its second best, and
+// gains only fall).  While applying the step's hits every block also sums
 // r's changes from the same terms, so every block holds the same lower bound
 // on r's gain after the step; if its truncated gain is strictly above U, r is
 // the next winner (whatever the indices), every block knows it, and the next
 // step runs without an exchange, on r's row of T loaded during this step.
-// The same holds down a chain: with r_1, r_2, ... the best candidates of
-// distinct blocks in key order (the winner's block left out), r_m follows
-// r_(m-1) when its bound beats the best key of the remaining blocks, r_(m+1),
-// and the second-best keys of the winner's block and of r_1 .. r_m; every
-// block tracks the changes of all of r_1 .. r_kChain since the exchange.
 __device__ __forceinline__ void publish_rows(const long long* sG, const unsigned char* ssel, int lo, int cnt, int S,
                                              unsigned long long* slot, unsigned long long epoch) {
   if (threadIdx.x >= 64) return;
-  const int i = threadIdx.x;
-  const bool ok = i < cnt && !ssel[i];
-  long long g1 = ok ? sG[i] : -1;
-  int i1 = ok ? lo + i : INT_MAX;
-  const long long mine = g1;
-  const int mi = i1;
-  wave_argmax(g1, i1);
-  long long g2 = mi == i1 ? -1 : mine;
-  int i2 = mi == i1 ? INT_MAX : mi;
-  wave_argmax(g2, i2);
-  if (i == 0) {
-    put(slot + 1, (i2 != INT_MAX ? pack_key(fx_to_double(g2, S), i2) : kNoCandidate) | epoch);
-    put(slot, (i1 != INT_MAX ? pack_key(fx_to_double(g1, S), i1) : kNoCandidate) | epoch);
-  }
+  const unsigned long long mine = column_key(sG, ssel, lo, threadIdx.x, cnt, S);
+  const unsigned long long k1 = wave_max_u64(mine);
+  const unsigned long long k2 = wave_max_u64(mine == k1 ? kNoCandidate : mine);
+  if (threadIdx.x < 2) put(slot + threadIdx.x, (threadIdx.x ? k2 : k1) | epoch);
 }
 
 // A lower bound on the fixed-point gain g behind a key: the key keeps the
@@ -425,8 +409,7 @@ __device__ int read_winner_rows(const unsigned long long* slots, unsigned long l
   return aborting ? -1 : int(kIndexMask - (m & kIndexMask));
 }
 
-constexpr int kChain = 1;   // predicted steps in a row at most (deeper chains measured slower)
-constexpr int kTrackMax = 256;   // hits of a step that still tracks the chain
+constexpr int kTrackMax = 256;   // hits of a step that still tracks the runner-up
 
 // The step-0 gains of a block's columns [lo, lo + cnt) from the P partial
 // sums part[q][column] (64-bit integers, so the split does not matter):
@@ -477,7 +460,6 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
   unsigned char* ssel = reinterpret_cast<unsigned char*>(sball + a.ldt);   // [W] chosen columns
   __shared__ long long red[kBlock];
   __shared__ long long sg[kWaves];
-  __shared__ int si[kWaves];
   __shared__ unsigned long long su[kWaves];
   __shared__ int sflag;
   __shared__ int lj[kCapR];                    // hit list: target
@@ -486,17 +468,13 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
   __shared__ int scnt[2];                     // hits listed in steps of each parity
   __shared__ int schunk[kRowsMaxN / kRowChunk];   // dense steps: hits per chunk, then their offsets
   if (tid == 0) scnt[0] = scnt[1] = 0;
-  // Prediction of the next winners (one column group only): every block's
-  // two slot words of the last exchange and the waves' parts of the chain
-  // candidates' changes in the step.
+  // Prediction of the next winner (one column group only): every block's
+  // slot words of the last exchange and the waves' parts of the runner-up's
+  // change in the step.
   constexpr bool kSpec = NG == 1;
   __shared__ unsigned long long sk1[kSpec ? kMaxBlocks : 1], sk2[kSpec ? kMaxBlocks : 1];
-  __shared__ long long sdr[kWaves][kChain];
+  __shared__ long long sdr[kWaves];
 
-  // A launch that continues another one runs only when its gate says so
-  // (the same word for every block), and then starts from the state the
-  // previous launch handed over.
-  if (a.gate && *a.gate != a.gate_val) return;
   // After the early kernel the first step is the one it stopped before.
   if (a.start && *a.abort) return;
   const int k_begin = a.start ? int(*a.start) : a.k_begin;
@@ -540,27 +518,20 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
     if (kSpec)
       publish_rows(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0));
     else
-      publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), sg, si);
+      publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), su);
   }
 
   const int nch = a.ldt / kRowChunk;
   bool predicted = false;     // this step's winner was predicted (no exchange)
   int tpred = -1;
   f32x4 xr2[RL];              // the predicted winner's row, loaded during the previous step
-  // The chain since the last exchange, the same in every wave and block:
-  // candidates r_1 .. (-1 past the last), lower bounds on their gains (with
-  // their changes since the exchange), the bounds they must beat (truncated
-  // gain bits), and the position (steps predicted since the exchange).
-  int rc[kChain];
-  long long acc[kChain];
-  unsigned long long ub[kChain];
-  int chain = 0;
-#pragma unroll
-  for (int m = 0; m < kChain; ++m) {
-    rc[m] = -1;
-    acc[m] = 0;
-    ub[m] = 0ull;
-  }
+  // The runner-up of the last exchange, the same in every wave and block
+  // (-1 when the step has none: it was predicted itself, or had many hits),
+  // the lower bound on its gain with the changes since, and the truncated
+  // gain it must exceed.
+  int rn = -1;
+  long long racc = 0;
+  unsigned long long rub = 0ull;
   for (int step = k_begin; step < a.k_end; ++step) {
     int tw;
     if (predicted) {
@@ -594,47 +565,36 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
     for (int i = 0; i < RL; ++i)
       if (w + i * kWaves < nch) xr[i] = predicted ? xr2[i] : row[(w + i * kWaves) * (kRowChunk / 4) + lane];
 
-    // After an exchange every wave builds the chain while the row is in
-    // flight: the best keys of distinct blocks in order, each taken out in
-    // turn.  Blocks own W consecutive columns, so the winner's block is t / W.
-    if (kSpec && !predicted) {
-      const int bt = block_of(a, t);
-      unsigned long long k[4];
+    // After an exchange every wave finds the runner-up while the row is in
+    // flight.  Blocks own W consecutive columns, so the winner's is t / W.
+    if (kSpec) {
+      rn = -1;
+      if (!predicted) {
+        const int bt = block_of(a, t);
+        unsigned long long k[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int b = lane + 64 * q;
-        k[q] = (b < nb && b != bt) ? sk1[b] : 0ull;
-      }
-      unsigned long long u2 = sk2[bt];
-      int bprev = -1;
-#pragma unroll
-      for (int m = 0; m <= kChain; ++m) {
+        for (int q = 0; q < 4; ++q) {
+          const int b = lane + 64 * q;
+          k[q] = (b < nb && b != bt) ? sk1[b] : 0ull;
+        }
         const unsigned long long kr = wave_max_u64(max(max(k[0], k[1]), max(k[2], k[3])));
-        const bool real = kr > kNoCandidate && (m == 0 || bprev >= 0);
-        const int r = real ? int(kIndexMask - (kr & kIndexMask)) : -1;
-        const int br = real ? block_of(a, r) : -1;
-        if (m > 0) ub[m - 1] = max(real ? kr : 0ull, u2) >> kIndexBits;
-        if (m < kChain) {
-          rc[m] = r;
-          acc[m] = real ? key_gain_floor(kr, S) : 0;
-          if (real) u2 = max(u2, sk2[br]);
+        if (kr > kNoCandidate) {
+          rn = min(int(kIndexMask - (kr & kIndexMask)), a.n - 1);
+          racc = key_gain_floor(kr, S);
+          const int br = block_of(a, rn);
 #pragma unroll
           for (int q = 0; q < 4; ++q) k[q] = (lane + 64 * q) == br ? 0ull : k[q];
+          const unsigned long long u = wave_max_u64(max(max(k[0], k[1]), max(k[2], k[3])));
+          rub = max(u, max(sk2[bt], sk2[br])) >> kIndexBits;
         }
-        bprev = br;
       }
-      chain = 0;
     }
 
     long long g[NG];
 #pragma unroll
     for (int q = 0; q < NG; ++q) g[q] = 0;
     long long dobj = 0;
-    long long dr[kChain];       // this wave's parts of the chain candidates' changes
-#pragma unroll
-    for (int m = 0; m < kChain; ++m) dr[m] = 0;
-    // Candidates still ahead in the chain: r_(chain+1) ..
-    auto live = [&](int m) { return kSpec && m >= chain && rc[m] >= 0; };
+    long long dr = 0;           // this wave's part of the runner-up's change
     // Applies listed hits base .. base + m to the wave's partial gains (and,
     // in block 0, to the objective), and records them in assign and (with
     // setb) in b.
@@ -644,22 +604,19 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
       // row reads are issued before the current batch's terms are summed.
       int jl = 0;
       float bol = 0.f, bnl = 0.f, vl = 0.f;
-      float rl[kChain];
+      float rl = 0.f;
       float xc[kChunk][NG];
       auto fetch = [&](int e0) {
         const int nbt = min(kChunk, base + m - e0);
         jl = 0;
         bol = bnl = vl = 0.f;
-#pragma unroll
-        for (int c = 0; c < kChain; ++c) rl[c] = 0.f;
+        rl = 0.f;
         if (lane < nbt) {
           jl = lj[e0 + lane];
           bol = lbo[e0 + lane];
           bnl = lbn[e0 + lane];
           vl = a.v[jl];
-#pragma unroll
-          for (int c = 0; c < kChain; ++c)
-            if (live(c)) rl[c] = a.C[size_t(jl) * a.n + rc[c]];   // C(r_c, j): a candidate's cost to the entry
+          if (kSpec && rn >= 0) rl = a.C[size_t(jl) * a.n + rn];   // C(r, j): the runner-up's cost to the entry
         }
 #pragma unroll
         for (int u = 0; u < kChunk; ++u) {
@@ -678,9 +635,7 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
         // batch, where v was not read).
         const double cvs = fx_scale(double(vl), S);
         const long long cvb = __double_as_longlong(cvs);
-        float cr[kChain];
-#pragma unroll
-        for (int c = 0; c < kChain; ++c) cr[c] = rl[c];
+        const float cr = rl;
         float cx[kChunk][NG];
 #pragma unroll
         for (int u = 0; u < kChunk; ++u)
@@ -704,13 +659,10 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
             }
           }
         }
-        // The batch's targets, one lane each: objective (block 0), the chain
-        // candidates' changes, b and assign.
+        // The batch's targets, one lane each: objective (block 0), the
+        // runner-up's change, b and assign.
         if (lane < nbt) {
-#pragma unroll
-          for (int c = 0; c < kChain; ++c)
-            if (live(c) && cr[c] < cbo)
-              dr[c] += fx_diff(cvs, fmaxf(cbn - cr[c], 0.f), cbo - cr[c]);
+          if (kSpec && rn >= 0 && cr < cbo) dr += fx_diff(cvs, fmaxf(cbn - cr, 0.f), cbo - cr);
           if (blk == 0) dobj += fx_diff(cvs, cbn, cbo);
           if (setb) sball[cj] = cbn;
           if (a.assign && unsigned(cj - lo) < unsigned(cnt)) a.assign[cj] = t;
@@ -754,9 +706,9 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
     }
     __syncthreads();
     const int total = scnt[par];
-    // Early steps improve many targets; tracking the chain there costs more
-    // than it saves, so a step with many hits ends the chain.
-    if (total > kTrackMax) chain = kChain;
+    // Early steps improve many targets; tracking the runner-up there costs
+    // more than it saves.
+    if (total > kTrackMax) rn = -1;
     if (tid == 0) scnt[par ^ 1] = 0;   // last read in the previous step, next used in the next
     if (total <= kCapR) {
       const int per = (total + kWaves - 1) / kWaves;
@@ -821,20 +773,11 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
       }
     }
 
-    // The next candidate, r_(chain+1), and its row for the next step if it
-    // is confirmed: issued after the step's own loads so that none of their
-    // waits includes it.
-    int rn = -1;
-#pragma unroll
-    for (int c = 0; c < kChain; ++c)
-      if (c == chain) rn = rc[c];
+    // The runner-up's row for the next step if it is confirmed: issued after
+    // the step's own loads so that none of their waits includes it.
     if (kSpec && rn >= 0) {
-#pragma unroll
-      for (int c = 0; c < kChain; ++c)
-        if (live(c)) {
-          const long long d = wave_sum_i64(dr[c]);
-          if (lane == 0) sdr[w][c] = d;
-        }
+      const long long d = wave_sum_i64(dr);
+      if (lane == 0) sdr[w] = d;
       const f32x4* rowr = reinterpret_cast<const f32x4*>(a.T + size_t(rn) * a.ldt);
 #pragma unroll
       for (int i = 0; i < RL; ++i)
@@ -863,35 +806,22 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
       obj_step = step;
     }
 
-    // The lower bounds on the candidates' gains after the step, the same in
-    // every block: when the next candidate's truncated gain beats its bound
-    // on all others, it is the next winner.
+    // The lower bound on the runner-up's gain after the step, the same in
+    // every block: above the bound on all others, it is the next winner.
     bool next = false;
     if (kSpec && rn >= 0) {
 #pragma unroll
-      for (int c = 0; c < kChain; ++c)
-        if (live(c))
-#pragma unroll
-          for (int q = 0; q < kWaves; ++q) acc[c] += sdr[q][c];
-      long long gr = 0;
-      unsigned long long u = 0ull;
-#pragma unroll
-      for (int c = 0; c < kChain; ++c)
-        if (c == chain) {
-          gr = acc[c];
-          u = ub[c];
-        }
-      next = step + 1 < a.k_end && gr > 0 && (pack_key(fx_to_double(gr, S), rn) >> kIndexBits) > u;
+      for (int q = 0; q < kWaves; ++q) racc += sdr[q];
+      next = step + 1 < a.k_end && racc > 0 && (pack_key(fx_to_double(racc, S), rn) >> kIndexBits) > rub;
     }
-    if (step + 1 < a.k && !next) {
+    if (step + 1 < a.k_end && !next) {
       if (kSpec)
         publish_rows(sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc));
       else
-        publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc), sg, si);
+        publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc), su);
     }
     predicted = next;
     tpred = rn;
-    chain += next ? 1 : 0;
   }
   __syncthreads();
   if (blk == 0 && tid == 0 && obj_step >= 0 && a.step_obj) {
@@ -914,7 +844,6 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
 #pragma unroll
         for (int q = 0; q < kWaves; ++q) L += sLw[q];
         a.ho_misc[0] = L;
-        a.ho_misc[1] = xc;
       }
     }
   }
@@ -954,25 +883,26 @@ constexpr int kEarlyMaxN = kRowChunk * kWaves * 8;    // 16384, the one-group ro
 constexpr int kEarlyCols = kEarlyMaxN / kBlock;       // columns per thread: 32
 constexpr int kEarlyPass = 8;                         // of which one pass over the share sums
 constexpr int kEarlyDepth = 4;                        // rows whose loads are in flight
-constexpr int kEarlyShare = 64;                       // hits a block takes per step at most (W <= 64)
+constexpr int kEarlyShare = 128;                      // hits a block takes per step at most
 constexpr int kEarlyMinHits = 512;                    // steps with fewer hits go back to the rows kernel
 
 int early_ldp(int64_t n) { return int((n + 1 + 63) / 64 * 64); }
-bool early_for(int64_t n, int W) { return n <= kEarlyMaxN && W <= 64; }
+bool early_for(int64_t n, int W) { return n <= kEarlyMaxN && W <= kRowsMaxW; }
 
-__global__ __launch_bounds__(kBlock) void sgs_early_kernel(IncDev a) {
+// NG 64-column groups per block, as in the rows kernel that continues.
+template <int NG>
+__device__ __forceinline__ void early_body(const IncDev& a, int blk, int nb) {
   extern __shared__ unsigned long long smem[];
   constexpr int RL = 8;                               // chunk loads per wave: n <= kRowChunk kWaves RL
-  const int blk = blockIdx.x, nb = gridDim.x;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int lo = blk * a.W;
   const int cnt = max(0, min(a.n, lo + a.W) - lo);
   long long* sG = reinterpret_cast<long long*>(smem);             // [W] running gains (W rounded up to even)
   float* sball = reinterpret_cast<float*>(sG + ((a.W + 1) & ~1));  // [ldt] b_j; -inf past n
   unsigned char* ssel = reinterpret_cast<unsigned char*>(sball + a.ldt);   // [W] chosen columns
-  __shared__ long long red[kBlock];
+  __shared__ long long red[NG * kBlock];
   __shared__ unsigned long long su[kWaves];
-  __shared__ unsigned long long sk1[kMaxBlocks], sk2[kMaxBlocks];
+  __shared__ unsigned long long sk1[NG == 1 ? kMaxBlocks : 1], sk2[NG == 1 ? kMaxBlocks : 1];
   __shared__ int sflag;
   __shared__ int schunk[kEarlyMaxN / kRowChunk];     // hits per chunk of the winner's row, then their offsets
   __shared__ int stot;
@@ -990,15 +920,22 @@ __global__ __launch_bounds__(kBlock) void sgs_early_kernel(IncDev a) {
     const long long x = fx_capacity_part(a.v, a.n, a.c0, S);
     L = block_sum_i64(x, red);
   }
-  publish_rows(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0));
+  auto publish = [&](int x) {
+    if (NG == 1)
+      publish_rows(sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x));
+    else
+      publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x), su);
+  };
+  publish(0);
 
   const int nch = a.ldt / kRowChunk;
   const int k_stop = a.k_end;                         // steps [0, k_stop) at most
   long long* mine = a.epart + size_t(blk) * a.ldp;
   int xc = 0;
   for (int step = 0; step < k_stop; ++step) {
-    const int tw = read_winner_rows(cand_slot(a.cand, xc & 1, 0), epoch_of(xc), nb, a.abort, a.poll_limit, su,
-                                    &sflag, sk1, sk2);
+    const unsigned long long* slots = cand_slot(a.cand, xc & 1, 0);
+    const int tw = NG == 1 ? read_winner_rows(slots, epoch_of(xc), nb, a.abort, a.poll_limit, su, &sflag, sk1, sk2)
+                           : read_winner(slots, epoch_of(xc), nb, a.abort, a.poll_limit, su, &sflag);
     ++xc;
     if (tw < 0) return;
     const int t = min(tw, a.n - 1);
@@ -1037,8 +974,9 @@ __global__ __launch_bounds__(kBlock) void sgs_early_kernel(IncDev a) {
     }
     __syncthreads();
     const int H = stot;
-    const int per = (H + nb - 1) / nb;                // at most ceil(n / nb) <= W
-    const int e_lo = min(H, blk * per), e_hi = min(H, e_lo + per);
+    const int ns = a.eshares;                         // blocks that may take a share
+    const int per = (H + ns - 1) / ns;                // at most ceil(n / ns) <= kEarlyShare
+    const int e_lo = min(H, blk * per), e_hi = blk < ns ? min(H, e_lo + per) : e_lo;
     const int nshare = per > 0 ? (H + per - 1) / per : 0;   // blocks with a share
     // The block's share of the list; every target's new best cost; assign
     // for the own targets.
@@ -1123,7 +1061,7 @@ __global__ __launch_bounds__(kBlock) void sgs_early_kernel(IncDev a) {
       }
       if (w == 0) {
         long long d = 0;
-        if (lane < nsh) d = fx_diff(svs[lane], sbn[lane], sbo[lane]);
+        for (int e = lane; e < nsh; e += 64) d += fx_diff(svs[e], sbn[e], sbo[e]);
         d = wave_sum_i64(d);
         if (lane == 0) put(reinterpret_cast<unsigned long long*>(mine + a.n), (unsigned long long)d);
       }
@@ -1149,26 +1087,30 @@ __global__ __launch_bounds__(kBlock) void sgs_early_kernel(IncDev a) {
       // nshare, or a column past cnt, is read from a valid address and not
       // summed).
       constexpr int kRead = 16;                       // loads in flight: two rounds for 256 blocks
-      const int col = min(lo + min(lane, max(cnt - 1, 0)), a.n - 1);
-      long long s = 0;
-      for (int b0 = 0; b0 < nshare; b0 += kRead * kWaves) {
-        unsigned long long x[kRead];
 #pragma unroll
-        for (int m = 0; m < kRead; ++m)
-          x[m] = get(reinterpret_cast<const unsigned long long*>(
-              a.epart + size_t(min(b0 + w + kWaves * m, nb - 1)) * a.ldp + col));
+      for (int q = 0; q < NG; ++q) {
+        const int own = q * 64 + lane;
+        const int col = min(lo + min(own, max(cnt - 1, 0)), a.n - 1);
+        long long s = 0;
+        for (int b0 = 0; b0 < nshare; b0 += kRead * kWaves) {
+          unsigned long long x[kRead];
 #pragma unroll
-        for (int m = 0; m < kRead; ++m)
-          if (lane < cnt && b0 + w + kWaves * m < nshare) s += (long long)x[m];
+          for (int m = 0; m < kRead; ++m)
+            x[m] = get(reinterpret_cast<const unsigned long long*>(
+                a.epart + size_t(min(b0 + w + kWaves * m, ns - 1)) * a.ldp + col));
+#pragma unroll
+          for (int m = 0; m < kRead; ++m)
+            if (own < cnt && b0 + w + kWaves * m < nshare) s += (long long)x[m];
+        }
+        red[q * kBlock + tid] = s;
       }
-      red[tid] = s;
     }
     if (blk == 0 && w == 1) {
       constexpr int kRead = kMaxBlocks / 64;
       unsigned long long x[kRead];
 #pragma unroll
       for (int m = 0; m < kRead; ++m)
-        x[m] = get(reinterpret_cast<const unsigned long long*>(a.epart + size_t(min(lane + 64 * m, nb - 1)) * a.ldp + a.n));
+        x[m] = get(reinterpret_cast<const unsigned long long*>(a.epart + size_t(min(lane + 64 * m, ns - 1)) * a.ldp + a.n));
       long long s = 0;
 #pragma unroll
       for (int m = 0; m < kRead; ++m)
@@ -1177,15 +1119,20 @@ __global__ __launch_bounds__(kBlock) void sgs_early_kernel(IncDev a) {
       if (lane == 0 && a.step_obj) a.step_obj[step] = fx_to_double(L, S);
     }
     __syncthreads();
-    if (tid < 64 && tid < cnt) {
-      long long s = sG[tid];
+    if (tid < 64) {
 #pragma unroll
-      for (int r = 0; r < kWaves; ++r) s += red[r * 64 + tid];
-      sG[tid] = s;
+      for (int q = 0; q < NG; ++q)
+        if (q * 64 + tid < cnt) {
+          long long s = sG[q * 64 + tid];
+#pragma unroll
+          for (int r = 0; r < kWaves; ++r) s += red[q * kBlock + r * 64 + tid];
+          sG[q * 64 + tid] = s;
+        }
     }
-    // The next exchange's candidates (wave 0, which also wrote the gains),
-    // unless this was the last step.
-    if (step + 1 < a.k) publish_rows(sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc));
+    if (NG > 1) __syncthreads();
+    // The next exchange's candidates (one column group: wave 0, which also
+    // wrote the gains), unless this was the last step.
+    if (step + 1 < a.k) publish(xc);
     if (step + 1 == k_stop || H < kEarlyMinHits) {
       // Hand over before step + 1.
       __syncthreads();
@@ -1206,52 +1153,87 @@ __global__ __launch_bounds__(kBlock) void sgs_early_kernel(IncDev a) {
   }
 }
 
+template <int NG>
+__global__ __launch_bounds__(kBlock) void sgs_early_kernel(IncDev a) { early_body<NG>(a, blockIdx.x, gridDim.x); }
+
 // ---------------------------------------------------------------------------
 // The rows schedule's later steps from candidate lists.
 //
 // Best costs only fall, so a pair (candidate c, target j) with C(c, j) >= b_j
-// never changes a gain again.  After kListStep steps few pairs are left (at
-// N = 16384, K = 1638: 44 per candidate on average, at most 5391 among one
-// block's 64 candidates).  The rows schedule then runs in two launches: the
-// first stops after kListStep steps and hands its state over (best costs,
-// running gains, chosen flags, objective, exchange count); list_build_kernel
-// writes every candidate's pairs (target, cost, the target's capacity) into
-// a list of at most kListMax entries; sgs_list_kernel runs the remaining steps
-// from the lists.  Per step a block reads the winner's list (a few KB, from
-// L2 for all but the first block of an XCD) instead of its 64 KB row of T, and
-// keeps the block's own pairs (up to kEntMax) in LDS indexed by target: the
-// thread that lowers a target's best cost from the winner's list also adds
-// the changes of the own candidates paired with that target, instead of
-// reading each hit row's segment over its columns from memory.  The terms are the fixed-point terms of the rows of T, so the picks
-// are the same.  When the lists do not fit (a candidate with more than
-// kListMax pairs, or a block with more than kEntMax), the build raises lfail
-// and the rows kernel continues instead (its launch is gated on lfail).
-constexpr int kListStep = 128;                        // steps before the lists
-constexpr int kListSlots = 256;                       // per candidate: a header and kListMax pairs
-constexpr int kListMax = kListSlots - 1;
-constexpr int kListMaxN = kRowChunk * kWaves * 8;     // 16384, the one-group rows kernel's reach
-constexpr int kOwnSets = 16;                          // own pairs a thread places at the start
-constexpr int kEntMax = kOwnSets * kBlock;            // own pairs a block holds: 8192
+// never changes a gain again.  After the first steps few pairs are left (at
+// n = 6272: 229 per candidate on average after 8 picks, 60 after 64, 18 after
+// 128).  The rows schedule then hands its state over (best costs, running
+// gains, chosen flags, objective); list_build_kernel writes every candidate's
+// pairs (target, cost) into a list, and sgs_list_kernel runs the remaining
+// steps from the lists.
+//
+// A step needs the exchange of candidates only because the gains of other
+// blocks' columns are not known.  The list kernel therefore takes many steps
+// per exchange: a round.  Each block publishes its kPub best candidates with
+// their exact gains; every block takes the same set of up to kSet best ones,
+// and the largest gain left outside the set as the bound (all comparisons by
+// gain_key, as in the exchanges of keys).  The lists of the
+// set are then held in registers, and every block
+// runs the greedy among them: the best of the set is the next pick as long as
+// its gain is above the bound (gains only fall, so no candidate outside can
+// catch up); its hits lower the best costs in LDS, the other candidates of the
+// set sum their changes from their own entries whose best cost fell, and the
+// block's own columns theirs from its pairs in LDS, indexed by target.  All
+// terms are the fixed-point terms of the rows of T, so the picks are the same.
+// A round takes about fourteen steps with kSet = 32 (nine with 16, six with 8;
+// the prune of 6272 tokens takes 2.07 ms with 32, 2.15 with 16).
+//
+// Bound by instruction issue and LDS latency: about 1.5 us a step at n = 4096
+// .. 16384, a round's exchange (poll 3 us, choosing the set 2 us, its lists
+// 2.5 us, publishing 1.5 us) included; with a step or a chain of up to three
+// predicted ones per exchange it took 2.1 to 2.8 us.  Two waves per SIMD
+// (256 threads leave the latencies bare: 1.3 x the time; one wave per list
+// and 1024 threads issue every uniform instruction four times per SIMD).
+//
+// A candidate with more pairs than a list holds keeps its row of T: it stays
+// out of the set (its gain enters the bound) until it is the best of all, and
+// is then picked alone, its hits read from that row.  A block whose own pairs
+// do not fit in LDS reads the segments of the hits' rows of the cost over its
+// own columns instead.
+constexpr int kListCap = 512;                         // pairs a list holds at most
+constexpr int kListBlock = 512;                       // threads of the list kernel: two waves per SIMD
+constexpr int kListWaves = kListBlock / 64;
+constexpr int kSet = 32;                              // candidates a round considers at most
+constexpr int kChunksPer = 8;                        // chunks of 64 list entries a wave holds
+constexpr int kSetChunks = kListWaves * kChunksPer;   // those of a set
+constexpr int kPub = 4;                               // candidates a block publishes
+constexpr int kPubWords = kPub + 3;                   // gains, indices, the best gain left out, list lengths
+constexpr int kKeyLow = 16;                           // low bits of a gain_key that compare second
+constexpr unsigned kKeyLowMask = (1u << kKeyLow) - 1u;
+constexpr int kHitCap = 96;                          // hits a wave collects before it applies them
+constexpr int kHitPick = kListCap / kListWaves;       // of one pick at most
+static_assert(kHitPick % 64 == 0 && kHitPick < kHitCap, "a pick's chunks are spread evenly over the waves");
+constexpr int kListMaxN = kRowChunk * kWaves * 8;     // 16384
+constexpr int kListLds = 134 * 1024;                  // dynamic LDS of the list kernel at most
 
-bool lists_for(int64_t n, int64_t k, int W) { return n <= kListMaxN && W <= 64 && k > kListStep; }
-
-// The list kernel's LDS: the best costs, the own pairs' first index per
-// target (16 bits each, targets 0 .. n), their costs and candidates.
+// The list kernel's LDS: gains and chosen flags of W columns, the best costs
+// and (n <= kListLdsV: beyond it they would halve the room for the pairs) the
+// capacities, the own pairs' first index per target (16 bits each, targets 0 .. n), their
+// costs and candidates.
+constexpr int kListLdsV = 8192;
 __host__ __device__ __forceinline__ int list_off_words(int n) { return (n + 2) / 2; }
-size_t list_lds(int64_t n) {
-  return size_t(rows_ldt(n)) * 4 + size_t(list_off_words(int(n))) * 4 + size_t(kEntMax) * 5;
+size_t list_lds_fixed(int64_t n, int W) {
+  return size_t((W + 1) & ~1) * 8 + size_t(rows_ldt(n)) * 4 * (n <= kListLdsV ? 2 : 1) +
+         size_t(list_off_words(int(n))) * 4 + size_t((W + 3) & ~3);
 }
+int list_ent(int64_t n, int W) { return int(std::min<size_t>(65535, (size_t(kListLds) - list_lds_fixed(n, W)) / 5)) & ~3; }
 
 // One wave per candidate: its pairs from its row of T against the handed
-// over best costs.  Also counts the pairs of each block of the list kernel.
+// over best costs, gathered in LDS and then written as a whole (the list may
+// lie at the start of the row itself).
 __global__ __launch_bounds__(256) void list_build_kernel(IncDev a) {
+  __shared__ uint2 sl[4][kListCap];
   if (*a.abort) return;
-  const int lane = threadIdx.x & 63;
-  const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int c = blockIdx.x * 4 + w;
   if (c >= a.n) return;
   const f32x4* row = reinterpret_cast<const f32x4*>(a.T + size_t(c) * a.ldt);
   const f32x4* bb = reinterpret_cast<const f32x4*>(a.ho_b);
-  unsigned long long* dst = a.lists + size_t(c) * (2 * kListSlots);
   const int nch = a.ldt / kRowChunk;
   const unsigned long long lt = (1ull << lane) - 1ull;
   int m = 0;
@@ -1260,7 +1242,7 @@ __global__ __launch_bounds__(256) void list_build_kernel(IncDev a) {
 #pragma unroll
     for (int u = 0; u < 8; ++u)
       if (q0 + u < nch) {
-        x[u] = __builtin_nontemporal_load(row + (q0 + u) * (kRowChunk / 4) + lane);   // T is read once here
+        x[u] = __builtin_nontemporal_load(row + (q0 + u) * (kRowChunk / 4) + lane);
         b[u] = bb[(q0 + u) * (kRowChunk / 4) + lane];
       }
 #pragma unroll
@@ -1272,124 +1254,225 @@ __global__ __launch_bounds__(256) void list_build_kernel(IncDev a) {
         const unsigned long long mk = __ballot(hit);
         if (hit) {
           const int pos = m + __popcll(mk & lt);
-          const int j = (q0 + u) * kRowChunk + 4 * lane + cc;
-          if (pos < kListMax) {
-            dst[2 * (1 + pos)] = (unsigned long long)(unsigned)j | ((unsigned long long)__float_as_uint(x[u][cc]) << 32);
-            dst[2 * (1 + pos) + 1] = (unsigned long long)__float_as_uint(a.v[j]);
-          }
+          if (pos < a.lcap) sl[w][pos] = uint2{unsigned((q0 + u) * kRowChunk + 4 * lane + cc), __float_as_uint(x[u][cc])};
         }
         m += __popcll(mk);
       }
     }
   }
-  if (lane == 0) {
-    dst[0] = (unsigned long long)m;
-    const unsigned int tot = atomicAdd(a.lblock + c / a.W, unsigned(m)) + unsigned(m);
-    if (m > kListMax || tot > unsigned(kEntMax)) atomicOr(a.lfail, 1u);
+  // The wave's own LDS writes are read back by the same wave.
+  __builtin_amdgcn_wave_barrier();
+  if (m <= a.lcap) {
+    uint2* dst = a.lists + size_t(c) * a.lstride;
+    for (int e = lane; e < m; e += 64) dst[e] = sl[w][e];
+  }
+  if (lane == 0) a.llen[c] = unsigned(m);
+}
+
+__device__ __forceinline__ int gain_bits(long long g) { return g < 0 ? -1 : __float_as_int(float(g)); }
+__device__ __forceinline__ long long lane_i64(long long x, int l) { return (long long)lane_u64((unsigned long long)x, l); }
+
+// The kPub best unchosen columns of the block, by (gain_key, smaller index),
+// and the gain of the best one left out.  Every thread counts, for one column, the columns
+// of its part that come before it (a maximum after another over one wave took
+// four times as long); wave 0 publishes.  Words kListWord + r hold the gains,
+// the next the own indices (8 bits each), then the rest's gain and the
+// lists' lengths (12 bits each).  64 NG columns at most; starts and ends a
+// phase between barriers of the whole block.
+template <int NG>
+__device__ __forceinline__ void publish_list(const unsigned long long* sG, const unsigned char* ssel,
+                                             const unsigned short* slen, int cnt, int* srank, int* stop,
+                                             unsigned long long* slot, unsigned long long epoch) {
+  constexpr int kCols = 64 * NG, kParts = kListBlock / kCols;
+  const int tid = threadIdx.x;
+  const int i = tid % kCols, part = tid / kCols;
+  if (tid < kPub + 1) stop[tid] = -1;
+  {
+    const int per = (cnt + kParts - 1) / kParts, m1 = min(cnt, (part + 1) * per);
+    // Chosen columns count as key 0.
+    const unsigned long long u = i < cnt && !ssel[i] ? gain_key((long long)sG[i]) : 0ull;
+    int before = 0;
+    for (int m = part * per; m < m1; ++m) {
+      const unsigned long long x = ssel[m] ? 0ull : gain_key((long long)sG[m]);
+      before += x + (m < i ? 1 : 0) > u ? 1 : 0;
+    }
+    // srank[i] was left at zero by the previous call.
+    if (i < cnt && u) atomicAdd(&srank[i], before);
+  }
+  lds_barrier();
+  if (tid < kCols) {
+    if (i < cnt && !ssel[i]) {
+      const int r = srank[i];
+      if (r <= kPub) stop[r] = i;
+    }
+    srank[i] = 0;
+  }
+  if (NG > 1) lds_barrier();
+  if (tid < 64) {
+    // The five columns, read back by the wave that wrote them.
+    int col[kPub + 1];
+#pragma unroll
+    for (int r = 0; r <= kPub; ++r) col[r] = stop[r];
+    unsigned idx = 0;
+    unsigned long long lens = 0;
+#pragma unroll
+    for (int r = 0; r < kPub; ++r)
+      if (col[r] >= 0) {
+        idx |= unsigned(col[r]) << (8 * r);
+        lens |= (unsigned long long)min(int(slen[col[r]]), 4095) << (12 * r);
+      }
+    // Lane r < kPub a gain, then indices, the rest's gain, lengths.
+    int c = -1;
+#pragma unroll
+    for (int r = 0; r < kPub; ++r)
+      if (tid == r) c = col[r];
+    if (tid == kPub + 1) c = col[kPub];
+    unsigned long long word = c >= 0 ? sG[max(c, 0)] : kNoGain;
+    if (tid == kPub) word = idx;
+    if (tid == kPub + 2) word = lens;
+    if (tid < kPubWords) put(slot + kListWord + tid, word | epoch);
   }
 }
 
-// The greedy's steps kListStep .. k - 1 from the lists (one block of eight
-// waves per compute unit, block b owning candidates [b W, (b + 1) W) as in
-// the rows kernel, W <= 64).
-//
-// Predicted steps, as in the rows kernel but up to kListChain in a row: after
-// an exchange the chain r_1, r_2, ... are the best candidates of distinct
-// blocks in key order (the winner's block left out).  r_m is the next winner
-// when a lower bound on its gain (its key, plus its exact changes since the
-// exchange) beats the key of r_(m+1) and the second-best keys of the
-// winner's block and of r_1 .. r_m's blocks.  Every block holds the lists of
-// the exchange's winner and of the chain in registers, so it sums the chain's
-// changes itself (an entry's target was hit when its best cost fell in the
-// step: the same terms as the owner applies), and a predicted step finds its
-// winner's hits in registers: no exchange and no memory latency.
-//
-// A step: the waves holding the winner's list lower the best costs of its
-// hits in LDS; after a barrier every thread compares its own pairs' and its
-// chain entries' last seen best costs with LDS and sums the changes (own
-// candidates into LDS, chain candidates per wave); after a second barrier
-// every thread updates the chain bounds and decides whether the next step is
-// predicted, and wave 0 folds the gains and publishes when it is not.
-constexpr int kListChain = 3;                         // predicted steps in a row at most
-constexpr int kSlotsPerSet = kBlock / kListSlots;    // lists the block's threads hold side by side
-constexpr int kListSets = (kListChain + kSlotsPerSet) / kSlotsPerSet;   // chain list entries a thread holds
-
-__global__ __launch_bounds__(kBlock) void sgs_list_kernel(IncDev a) {
-  if (*a.lfail || *a.abort) return;
+// Steps k_begin .. k - 1 of a scene from the lists, by block `blk` of the
+// scene's `nb` blocks (NG columns per lane: W <= 64 NG).
+template <int NG>
+__device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
+  if (*a.abort || a.k_begin >= a.k) return;
   extern __shared__ unsigned long long smem[];
-  const int blk = blockIdx.x, nb = gridDim.x;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lo = blk * a.W;
   const int cnt = max(0, min(a.n, lo + a.W) - lo);
-  float* sball = reinterpret_cast<float*>(smem);                   // [ldt] best costs
+  unsigned long long* sG = smem;                                   // [W] running gains (W rounded up to even)
+  float* sball = reinterpret_cast<float*>(sG + ((a.W + 1) & ~1));  // [ldt] best costs
   // The block's own pairs by target: pairs [off(j), off(j + 1)) have target
   // j, each with its cost and its candidate (own index); off as 16-bit
   // values, two to a word.
-  unsigned int* soffw = reinterpret_cast<unsigned int*>(sball + a.ldt);   // [n / 2 + 1]
-  float* spc = reinterpret_cast<float*>(soffw + list_off_words(a.n));     // [kEntMax]
-  unsigned char* spk = reinterpret_cast<unsigned char*>(spc + kEntMax);   // [kEntMax]
+  const bool v_lds = a.n <= kListLdsV;
+  float* sv = sball + a.ldt;                                       // [ldt] capacities (v_lds)
+  unsigned int* soffw = reinterpret_cast<unsigned int*>(v_lds ? sv + a.ldt : sv);
+  unsigned char* ssel = reinterpret_cast<unsigned char*>(soffw + list_off_words(a.n));   // [W] chosen
+  float* spc = reinterpret_cast<float*>(ssel + ((a.W + 3) & ~3));  // [lent]
+  unsigned char* spk = reinterpret_cast<unsigned char*>(spc + a.lent);    // [lent]
   auto off = [&](int j) { return int((soffw[j >> 1] >> ((j & 1) * 16)) & 0xffffu); };
-  __shared__ long long sG[64];
-  __shared__ unsigned char ssel[64];
-  __shared__ unsigned long long sdelta[2][64];                      // own gain changes, by step parity
-  __shared__ int soff[65];                                          // each own candidate's first pair
-  __shared__ int swt[kWaves];
-  __shared__ unsigned long long su[kWaves], sk1[kMaxBlocks], sk2[kMaxBlocks];
-  __shared__ int sflag;
+  __shared__ int soff[64 * NG + 1];                                 // each own candidate's first listed pair
+  __shared__ int swt[kListWaves];
+  // What a round reads from the exchange, and then, in the same memory, the
+  // hits and changes its waves list.
+  struct Exchange {
+    unsigned long long gain[kPub + 1][kMaxBlocks];                  // gains, best gain left out
+    unsigned long long len[kMaxBlocks];                             // list lengths
+    int bits[kPub][kMaxBlocks];                                     // gain_bits of the gains
+    unsigned idx[kMaxBlocks];                                       // indices
+  };
+  struct Picks {
+    uint4 hit[kListWaves][kHitCap];                                 // target | pick << 16, new, old cost, capacity
+    uint4 chg[kListWaves][64];                                      // a wave's changes: cost, new, old best, capacity
+    int chm[kListWaves][64];                                        // and member
+  };
+  __shared__ union Round {
+    Exchange x;
+    Picks p;
+  } sr;
+  auto& sgw = sr.x.gain;
+  auto& sgl = sr.x.len;
+  auto& sgf = sr.x.bits;
+  auto& sgi = sr.x.idx;
+  auto& shit = sr.p.hit;
+  auto& schg = sr.p.chg;
+  auto& schm = sr.p.chm;
+  __shared__ unsigned long long sset[kSet];                         // the set's gains
+  __shared__ int sidx[kSet], slist[kSet];                           // indices and list lengths
+  __shared__ long long sbound[4];
+  __shared__ int sflag, stotal;
+  __shared__ int spt[kSet];                                         // the round's picks
+  __shared__ long long spg[kSet];                                   // their gains
+  __shared__ unsigned long long sobj[kSet];                         // and changes of the objective (block 0)
   __shared__ unsigned long long sL;                                 // objective (block 0)
-  __shared__ unsigned long long sacc[kListChain + 1];               // chain changes since the exchange
+  __shared__ int srank[64 * NG], stop5[kPub + 1];                   // publish_list's
+  __shared__ unsigned short slen[64 * NG];                          // own candidates' pairs, 65535 for more
   const int S = *a.scale;
 
-  for (int j = tid; j < a.ldt; j += kBlock) sball[j] = a.ho_b[j];
-  for (int i = tid; i < list_off_words(a.n); i += kBlock) soffw[i] = 0u;
-  if (tid < 64) {
-    ssel[tid] = tid < cnt ? a.ho_sel[lo + tid] : 1;
-    sG[tid] = tid < cnt ? a.ho_gain[lo + tid] : 0;
-    sdelta[0][tid] = sdelta[1][tid] = 0ull;
-    // Where each own candidate's pairs start among the block's.
-    const int m = tid < cnt ? min(int(a.lists[size_t(lo + tid) * (2 * kListSlots)]), kListMax) : 0;
-    const int incl = wave_scan_incl(m);
-    soff[tid + 1] = incl;
-    if (tid == 0) soff[0] = 0;
+  for (int j = tid; j < a.ldt; j += kListBlock) {
+    sball[j] = a.ho_b[j];
+    if (v_lds) sv[j] = j < a.n ? a.v[j] : 0.f;
   }
-  if (tid == 0) sL = (unsigned long long)(blk == 0 ? a.ho_misc[0] : 0);
-  __syncthreads();
-  const int npairs = min(soff[64], kEntMax);
-  {
-    // Pair p = q kBlock + tid of the block (candidates in order, each with
-    // its list's entries): its candidate by a search of soff, its entry from
-    // the list; all loads issued before any is used.
-    int ci[kOwnSets], e[kOwnSets];
-#pragma unroll
-    for (int q = 0; q < kOwnSets; ++q) {
-      const int pq = q * kBlock + tid;
-      int c = 0;
-#pragma unroll
-      for (int st = 32; st > 0; st >>= 1)
-        if (c + st < 64 && soff[c + st] <= pq) c += st;
-      ci[q] = c;
-      e[q] = pq < npairs ? 1 + pq - soff[c] : 0;
+  for (int i = tid; i < list_off_words(a.n); i += kListBlock) soffw[i] = 0u;
+  if (tid < kSet) sobj[tid] = 0ull;
+  if (tid < 64 * NG) srank[tid] = 0;
+  if (tid == 0) {
+    sflag = 0;
+    sL = (unsigned long long)(blk == 0 ? a.ho_misc[0] : 0);
+  }
+  // Own candidates' pair counts: all of them (do they fit?) and the listed ones.
+  if (w == 0) {
+    int run = 0, all = 0;
+    for (int q = 0; q < NG; ++q) {
+      const int i = q * 64 + lane;
+      const int m = i < cnt ? int(a.llen[lo + i]) : 0;
+      const bool lng = m > a.lcap;
+      if (i < cnt) {
+        ssel[i] = a.ho_sel[lo + i];
+        slen[i] = (unsigned short)min(m, 65535);
+        sG[i] = (unsigned long long)a.ho_gain[lo + i];
+      }
+      const int incl = wave_scan_incl(lng ? 0 : m);
+      soff[i + 1] = run + incl;
+      run += __builtin_amdgcn_readlane(incl, 63);
+      all += __builtin_amdgcn_readlane(wave_scan_incl(m), 63);
     }
-    uint2 ev[kOwnSets];
-#pragma unroll
-    for (int q = 0; q < kOwnSets; ++q)
-      ev[q] = reinterpret_cast<const uint2*>(a.lists + size_t(min(lo + ci[q], a.n - 1)) * (2 * kListSlots))[2 * e[q]];
+    if (lane == 0) {
+      soff[0] = 0;
+      stotal = all;
+    }
+  }
+  __syncthreads();
+  const bool own_lds = stotal <= a.lent;                            // uniform over the block
+  if (own_lds) {
     // Pairs per target (16-bit counts, two to a word), their inclusive
     // prefix over the targets, then each pair placed at its target's end,
-    // which moves down to the target's first pair.
+    // which moves down to the target's first pair.  A long candidate's pairs
+    // come from its row of T.
+    const int npairs = soff[64 * NG];
+    auto each_pair = [&](auto f) {
+      for (int p0 = 0; p0 < npairs; p0 += 8 * kListBlock) {
+        uint2 ev[8];
+        int ci[8];
 #pragma unroll
-    for (int q = 0; q < kOwnSets; ++q)
-      if (q * kBlock + tid < npairs) {
-        const int j = min(int(ev[q].x), a.n - 1);
-        atomicAdd(&soffw[j >> 1], 1u << ((j & 1) * 16));
+        for (int q = 0; q < 8; ++q) {
+          const int pq = min(p0 + q * kListBlock + tid, npairs - 1);
+          int c = 0;
+#pragma unroll
+          for (int st = 32 * NG; st > 0; st >>= 1)
+            if (c + st < 64 * NG && soff[c + st] <= pq) c += st;
+          ci[q] = c;
+          ev[q] = a.lists[size_t(lo + c) * a.lstride + (pq - soff[c])];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          if (p0 + q * kListBlock + tid < npairs) f(min(int(ev[q].x), a.n - 1), __uint_as_float(ev[q].y), ci[q]);
       }
+      for (int i = 0; i < cnt; ++i)
+        if (int(slen[i]) > a.lcap)
+          for (int j = tid; j < a.n; j += kListBlock) {
+            const float x = a.T[size_t(lo + i) * a.ldt + j];
+            if (x < sball[j]) f(j, x, i);
+          }
+    };
+    each_pair([&](int j, float, int) { atomicAdd(&soffw[j >> 1], 1u << ((j & 1) * 16)); });
     __syncthreads();
-    const int per = (list_off_words(a.n) + kBlock - 1) / kBlock;   // words a thread scans
+    const int per = (list_off_words(a.n) + kListBlock - 1) / kListBlock;   // words a thread scans
+    const int w0 = min(tid * per, list_off_words(a.n)), w1 = min(w0 + per, list_off_words(a.n));
     int sum = 0;
-    for (int i = tid * per; i < min((tid + 1) * per, list_off_words(a.n)); ++i)
-      sum += int(soffw[i] & 0xffffu) + int(soffw[i] >> 16);
-    int run = block_inclusive_scan(sum, swt) - sum;
-    for (int i = tid * per; i < min((tid + 1) * per, list_off_words(a.n)); ++i) {
+    for (int i = w0; i < w1; ++i) sum += int(soffw[i] & 0xffffu) + int(soffw[i] >> 16);
+    const int incl = wave_scan_incl(sum);
+    if (lane == 63) swt[w] = incl;
+    __syncthreads();
+    int run = incl - sum;
+#pragma unroll
+    for (int q = 0; q < kListWaves; ++q)
+      if (q < w) run += swt[q];
+    for (int i = w0; i < w1; ++i) {
       const unsigned int wv = soffw[i];
       const int lo16 = run + int(wv & 0xffffu);
       const int hi16 = lo16 + int(wv >> 16);
@@ -1397,200 +1480,442 @@ __global__ __launch_bounds__(kBlock) void sgs_list_kernel(IncDev a) {
       run = hi16;
     }
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kOwnSets; ++q)
-      if (q * kBlock + tid < npairs) {
-        const int j = min(int(ev[q].x), a.n - 1);
-        const unsigned int sh = (j & 1) * 16;
-        const int pos = int((atomicSub(&soffw[j >> 1], 1u << sh) >> sh) & 0xffffu) - 1;
-        spc[pos] = __uint_as_float(ev[q].y);
-        spk[pos] = (unsigned char)ci[q];
-      }
+    each_pair([&](int j, float x, int i) {
+      const unsigned int sh = (j & 1) * 16;
+      const int pos = int((atomicSub(&soffw[j >> 1], 1u << sh) >> sh) & 0xffffu) - 1;
+      spc[pos] = x;
+      spk[pos] = (unsigned char)i;
+    });
     __syncthreads();
   }
 
-  // Chain slots: 0 the exchange's winner, m = 1 .. kListChain the candidate
-  // r_m (-1 past the last), with lower bounds on their gains at the exchange
-  // and the key bits they must beat.  Entry set q of a thread is entry
-  // tid % kListSlots of slot q kSlotsPerSet + tid / kListSlots's list:
-  // target, cost, scaled capacity, and the target's best cost as last seen
-  // (entry 0 of a list is its header).
-  const int half = tid / kListSlots, ent = tid % kListSlots;
-  int rc[kListChain + 1];
-  long long acc[kListChain + 1];
-  unsigned long long ub[kListChain + 1];
-  int ej[kListSets];
-  float ec[kListSets], eb[kListSets];
-  double evs[kListSets];
-  bool eok[kListSets];
+  // The own columns' changes of a wave's hits (a lane each, where ok) when
+  // the pairs are not in LDS: the hits' rows of the cost, eight at a time.
+  auto own_segments = [&](bool ok, int j, float x, float bo, double vs) {
+    unsigned long long mk = __ballot(ok);
+    const long long vb = __double_as_longlong(vs);
+    long long g[NG];
 #pragma unroll
-  for (int m = 0; m <= kListChain; ++m) {
-    rc[m] = -1;
-    acc[m] = 0;
-    ub[m] = 0ull;
-  }
+    for (int q = 0; q < NG; ++q) g[q] = 0;
+    while (mk) {
+      int ln[8];
+      float cv[8][NG];
 #pragma unroll
-  for (int q = 0; q < kListSets; ++q) {
-    ej[q] = 0;
-    ec[q] = eb[q] = 0.f;
-    evs[q] = 0.0;
-    eok[q] = false;
-  }
-  int xc = int(a.ho_misc[1]);
-  int obj_step = a.k_begin - 1;
-  bool predicted = false;
-  int pos = 0;                 // the step's place in the chain (0: after an exchange)
-  for (int step = a.k_begin; step < a.k; ++step) {
-    int t = -1;
-    const int par = step & 1;
-    if (!predicted) {
-      const int tw = read_winner_rows(cand_slot(a.cand, xc & 1, 0), epoch_of(xc), nb, a.abort, a.poll_limit, su,
-                                      &sflag, sk1, sk2);
-      ++xc;
-      if (tw < 0) break;
-      t = min(tw, a.n - 1);
-      if (tid <= kListChain) sacc[tid] = 0ull;
-      // The chain from the exchange's keys (every wave the same).
-      const int bt = block_of(a, t);
-      unsigned long long kq[4];
+      for (int u = 0; u < 8; ++u) {
+        ln[u] = mk ? __builtin_ctzll(mk) : -1;
+        mk = mk ? mk & (mk - 1) : 0ull;
+        const int jr = __builtin_amdgcn_readlane(j, max(ln[u], 0));
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int bq = lane + 64 * q;
-        kq[q] = (bq < nb && bq != bt) ? sk1[bq] : 0ull;
+        for (int q = 0; q < NG; ++q)
+          cv[u][q] = (ln[u] >= 0 && q * 64 + lane < cnt) ? a.C[size_t(jr) * a.n + lo + q * 64 + lane] : __builtin_inff();
       }
-      unsigned long long u2 = sk2[bt];
-      rc[0] = t;
 #pragma unroll
-      for (int m = 1; m <= kListChain + 1; ++m) {
-        const unsigned long long kr = wave_max_u64(max(max(kq[0], kq[1]), max(kq[2], kq[3])));
-        const bool real = kr > kNoCandidate && (m == 1 || rc[m - 1] >= 0);
-        const int r = real ? int(kIndexMask - (kr & kIndexMask)) : -1;
-        const int br = real ? block_of(a, r) : -1;
-        if (m >= 2) ub[m - 1] = max(real ? kr : 0ull, u2) >> kIndexBits;
-        if (m <= kListChain) {
-          rc[m] = r;
-          acc[m] = real ? key_gain_floor(kr, S) : 0;
-          if (real) u2 = max(u2, sk2[br]);
+      for (int u = 0; u < 8; ++u) {
+        const int l = max(ln[u], 0);
+        const float bor = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bo), l));
+        const float xr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
+        const double vr = __longlong_as_double(
+            (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane(int(vb >> 32), l) << 32) |
+                        (unsigned)__builtin_amdgcn_readlane(int(vb), l)));
 #pragma unroll
-          for (int q = 0; q < 4; ++q) kq[q] = (lane + 64 * q) == br ? 0ull : kq[q];
+        for (int q = 0; q < NG; ++q)
+          if (cv[u][q] < bor) g[q] += fx_diff(vr, fmaxf(xr - cv[u][q], 0.f), bor - cv[u][q]);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+      if (g[q] != 0) atomicAdd(&sG[q * 64 + lane], (unsigned long long)g[q]);
+  };
+  // A wave's hits, one a lane (where ok): at its pick (the round's ord-th)
+  // target j fell from bo to x; v is its capacity.  The own columns' gains and
+  // (block 0) the objective.
+  auto apply_hits = [&](bool ok, int ord, int j, float x, float bo, float v) {
+    const double vs = fx_scale(double(v), S);
+    if (ok && own_lds) {
+      const int p1 = off(j + 1);
+      for (int p = off(j); p < p1; ++p) {
+        const float cv = spc[p];
+        if (cv < bo) atomicAdd(&sG[spk[p]], (unsigned long long)fx_diff(vs, fmaxf(x - cv, 0.f), bo - cv));
+      }
+    }
+    if (!own_lds) own_segments(ok, j, x, bo, vs);
+    if (blk == 0 && ok) atomicAdd(&sobj[ord], (unsigned long long)fx_diff(vs, x, bo));
+  };
+
+  // Hits a wave has listed: their consequences, and the assignment of the own
+  // targets (by the last pick that lowered each: the one whose cost stands).
+  auto flush = [&](int nh) {
+    for (int e0 = 0; e0 < nh; e0 += 64) {
+      const bool ok = e0 + lane < nh;
+      const uint4 h = shit[w][ok ? e0 + lane : 0];
+      const int j = int(h.x & 0xffffu), ord = int(h.x >> 16);
+      const float x = __uint_as_float(h.y);
+      apply_hits(ok, ord, j, x, __uint_as_float(h.z), __uint_as_float(h.w));
+      if (ok && a.assign && unsigned(j - lo) < unsigned(cnt) && sball[j] == x) a.assign[j] = spt[ord];
+    }
+  };
+
+  int step = a.k_begin;
+  int gap = 1 << 20;                                                // the last round's threshold below its best
+  publish_list<NG>(sG, ssel, slen, cnt, srank, stop5, cand_slot(a.cand, 0, blk), epoch_of(0));
+  for (int xc = 0; step < a.k; ++xc) {
+    // The exchange: a wave reads eight slots per load, eight lanes each.
+    {
+      const unsigned long long ep = epoch_of(xc);
+      const unsigned long long* slots = cand_slot(a.cand, xc & 1, 0) + kListWord;
+      constexpr int kRead = kMaxBlocks / (8 * kListWaves);          // loads in flight: 8
+      const int r = lane & 7;
+      unsigned long long x[kRead];
+      bool need[kRead];
+#pragma unroll
+      for (int q = 0; q < kRead; ++q) {
+        need[q] = r < kPubWords && (w * kRead + q) * 8 + (lane >> 3) < nb;
+        x[q] = ~ep;
+      }
+      for (unsigned int spins = 0;; ++spins) {
+        bool miss = false;
+#pragma unroll
+        for (int q = 0; q < kRead; ++q)
+          if (need[q] && (x[q] & kEpoch) != ep)
+            x[q] = get(slots + size_t((w * kRead + q) * 8 + (lane >> 3)) * kSlotStride + r);
+#pragma unroll
+        for (int q = 0; q < kRead; ++q) miss = miss || (need[q] && (x[q] & kEpoch) != ep);
+        if (!__ballot(miss)) break;
+        if (__ballot(give_up(spins, a.poll_limit, a.abort))) {
+          if (lane == 0) sflag = 1;
+          break;
         }
-      }
-      pos = 0;
-      // The lists of the winner and of the chain, all loads in flight
-      // together (plain loads: the lists are fixed since the build).
-      uint4 hv[kListSets], ev[kListSets];
-#pragma unroll
-      for (int q = 0; q < kListSets; ++q) {
-        const int sl = q * kSlotsPerSet + half;
-        int r = -1;
-#pragma unroll
-        for (int m = 0; m <= kListChain; ++m)
-          if (m == sl) r = rc[m];
-        const uint4* lw = reinterpret_cast<const uint4*>(a.lists + size_t(max(r, 0)) * (2 * kListSlots));
-        hv[q] = lw[0];
-        ev[q] = lw[ent];
-        eok[q] = r >= 0;
+        __builtin_amdgcn_s_sleep(1);
       }
 #pragma unroll
-      for (int q = 0; q < kListSets; ++q) {
-        eok[q] = eok[q] && ent >= 1 && ent <= min(int(hv[q].x), kListMax);
-        ej[q] = eok[q] ? min(int(ev[q].x), a.n - 1) : 0;
-        ec[q] = __uint_as_float(ev[q].y);
-        evs[q] = fx_scale(double(__uint_as_float(ev[q].z)), S);
-      }
-      // The entries' best costs before the step's hits lower them.
-#pragma unroll
-      for (int q = 0; q < kListSets; ++q) eb[q] = eok[q] ? sball[ej[q]] : 0.f;
-      __syncthreads();
-    } else {
-#pragma unroll
-      for (int m = 1; m <= kListChain; ++m)
-        if (m == pos) t = rc[m];
-    }
-    if (blk == 0 && tid == 0 && obj_step >= 0 && a.step_obj) a.step_obj[obj_step] = fx_to_double((long long)sL, S);
-    if (t >= lo && t < lo + cnt && tid == 0) {
-      ssel[t - lo] = 1;
-      a.selected[step] = t;
-      if (a.step_gain) a.step_gain[step] = fx_to_double(sG[t - lo], S);
-    }
-    // The winner's hits, from the waves that hold its list (slot pos): each
-    // lowers its target's best cost (a target appears once in a list).
-    long long dobj = 0;
-#pragma unroll
-    for (int q = 0; q < kListSets; ++q) {
-      if (q * kSlotsPerSet + half != pos) continue;   // uniform over the wave
-      if (eok[q]) {
-        const int j = ej[q];
-        const float x = ec[q], bo = sball[j];
-        if (x < bo) {
-          sball[j] = x;
-          if (blk == 0) dobj = fx_diff(evs[q], x, bo);
-          if (a.assign && unsigned(j - lo) < unsigned(cnt)) a.assign[j] = t;
-          // The own candidates with a pair on j: their gain changes, added
-          // up in LDS as 64-bit integers.
-          const int p1 = off(j + 1);
-          for (int p = off(j); p < p1; ++p) {
-            const float cv = spc[p];
-            if (cv < bo)
-              atomicAdd(&sdelta[par][spk[p]], (unsigned long long)fx_diff(evs[q], fmaxf(x - cv, 0.f), bo - cv));
+      for (int q = 0; q < kRead; ++q)
+        if (r < kPubWords) {
+          // Blocks past nb publish nothing.
+          const int b = (w * kRead + q) * 8 + (lane >> 3);
+          x[q] = need[q] ? x[q] & ~kEpoch : (r == kPub || r == kPub + 2) ? 0ull : kNoGain;
+          if (r < kPub) {
+            sgw[r][b] = x[q];
+            sgf[r][b] = gain_bits(word_gain(x[q]));
+          } else if (r == kPub) {
+            sgi[b] = unsigned(x[q]);
+          } else if (r == kPub + 1) {
+            sgw[kPub][b] = x[q];
+          } else {
+            sgl[b] = x[q];
           }
         }
+    }
+    lds_barrier();
+    if (sflag) break;
+    // The set: the candidates above a float threshold, found by bisection on
+    // the blocks' best ones (the same in every wave) so that at most kSet lie
+    // above it and their lists fit; wave w enters those of blocks 64 w ..
+    // 64 w + 63.  One without a list stays out.
+    int ns = 0;
+    {
+      int f[kPub][4], nc[kPub][4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const unsigned long long ln = sgl[lane + 64 * q];
+#pragma unroll
+        for (int r = 0; r < kPub; ++r) {
+          const int l = int(ln >> (12 * r)) & 0xfff;
+          f[r][q] = l > a.lcap ? -1 : sgf[r][lane + 64 * q];
+          nc[r][q] = max(1, (l + 63) >> 6);
+        }
+      }
+      const int ob = (w & 3) * 64 + lane;
+      unsigned long long og[kPub + 1];
+#pragma unroll
+      for (int r = 0; r <= kPub; ++r) og[r] = sgw[r][ob];
+      const unsigned oi = sgi[ob];
+      const unsigned long long ol = sgl[ob];
+      const int M = int(wave_max_u32(unsigned(max(max(f[0][0], f[0][1]), max(f[0][2], f[0][3])) + 1))) - 1;
+      auto count1 = [&](int T) {
+        int c = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c += __popcll(__ballot(f[0][q] > T));
+        return c;
+      };
+      constexpr int kLow = kSet * 5 / 8, kHigh = kSet - 2;          // of the blocks' best ones
+      int lo_t = -1, hi_t = M, T = max(-1, M - gap);
+      bool low = false;                                             // count1(lo_t) is known to be too many
+      for (int it = 0; it < 64; ++it) {
+        const int c = count1(T);
+        if (c > kHigh) {
+          lo_t = T;
+          low = true;
+        } else if (c < kLow && T > -1) {
+          hi_t = T;
+        } else {
+          break;
+        }
+        if (hi_t - lo_t <= 1) {
+          T = hi_t;
+          break;
+        }
+        // Without a lower end yet: twice as far below the best.
+        T = low ? lo_t + (hi_t - lo_t) / 2 : M - T > (1 << 28) ? -1 : max(-1, M - 2 * (M - T));
+      }
+      gap = max(1, M - T);
+      int base = 0;                                                 // members of the waves before
+      for (;;) {
+        ns = base = 0;
+        int ch = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (q == w) base = ns;
+#pragma unroll
+          for (int r = 0; r < kPub; ++r) {
+            ns += __popcll(__ballot(f[r][q] > T));
+            ch += f[r][q] > T ? nc[r][q] : 0;
+          }
+        }
+        if (ns <= kSet && wave_sum_i32(ch) <= kSetChunks) break;
+        T += (M - T + 1) / 2;                                       // none lies above M
+      }
+      if (w < 4) {
+        long long bound = word_gain(og[kPub]);
+#pragma unroll
+        for (int r = 0; r < kPub; ++r) {
+          const long long g = word_gain(og[r]);
+          const int l = int(ol >> (12 * r)) & 0xfff;
+          const bool in = l <= a.lcap && sgf[r][ob] > T;
+          const unsigned long long mk = __ballot(in);
+          if (in) {
+            const int at = base + __popcll(mk & ((1ull << lane) - 1ull));
+            sset[at] = (unsigned long long)g;
+            sidx[at] = min(ob * a.W + int((oi >> (8 * r)) & 0xffu), a.n - 1);
+            slist[at] = l;
+          } else {
+            bound = max(bound, g);
+          }
+          base += __popcll(mk);
+        }
+        bound = (long long)wave_max_u64((unsigned long long)(bound + 1)) - 1;
+        if (lane == 0) sbound[w] = bound;
+      }
+    }
+    lds_barrier();
+    long long bound = sbound[0];
+#pragma unroll
+    for (int q = 1; q < 4; ++q) bound = max(bound, sbound[q]);
+    const unsigned long long bkey = gain_key(bound);
+    int np = 0;                                                     // picks of the round
+    {
+      // The set's lists in chunks of 64 entries, member after member: chunk c
+      // in wave c mod kListWaves.  Target, cost, capacity and the target's best cost
+      // as last seen; lane m < ns looks after member m.
+      const bool mine = lane < ns;
+      const int myidx = mine ? sidx[lane & (kSet - 1)] : INT_MAX;
+      const int mylen = mine ? slist[lane & (kSet - 1)] : 0;
+      const int mych = (mylen + 63) >> 6;
+      const int myend = wave_scan_incl(mych), mystart = myend - mych;
+      const int nch = __builtin_amdgcn_readlane(myend, 63);
+      int mem[kChunksPer];                                          // uniform
+      int ej[kChunksPer];
+      float ec[kChunksPer], eb[kChunksPer], ev[kChunksPer];
+      {
+        uint2 en[kChunksPer];
+        int left[kChunksPer];
+#pragma unroll
+        for (int i = 0; i < kChunksPer; ++i) {
+          const int c = i * kListWaves + w;
+          mem[i] = -1;
+          if (c >= nch) continue;
+          const int m = __builtin_ctzll(__ballot(myend > c));
+          const int o = (c - __builtin_amdgcn_readlane(mystart, m)) * 64;
+          const uint2* l = a.lists + size_t(__builtin_amdgcn_readlane(myidx, m)) * a.lstride + o;
+          left[i] = __builtin_amdgcn_readlane(mylen, m) - o;
+          mem[i] = m;
+          en[i] = l[min(lane, left[i] - 1)];
+        }
+#pragma unroll
+        for (int i = 0; i < kChunksPer; ++i) {
+          ej[i] = 0;
+          ec[i] = __builtin_inff();
+          ev[i] = 0.f;
+          eb[i] = -__builtin_inff();
+          if (i * kListWaves + w >= nch) continue;
+          if (lane < left[i]) {
+            ej[i] = min(int(en[i].x), a.n - 1);
+            ec[i] = __uint_as_float(en[i].y);
+          }
+          ev[i] = v_lds ? sv[ej[i]] : a.v[ej[i]];
+          eb[i] = sball[ej[i]];
+        }
+      }
+      unsigned done = 0;                                            // members picked
+      int nh = 0;                                                   // hits this wave has listed
+      lds_barrier();   // every wave has read the best costs before the first pick lowers any
+      for (;; ++np) {
+        // The best of the set, the same in every wave: the largest high word
+        // of the keys, then (rarely) the low word, then the smallest index.
+        const long long gl = mine && !((done >> (lane & 31)) & 1u) ? (long long)sset[lane & (kSet - 1)] : -1;
+        const unsigned long long u = gain_key(gl);
+        const unsigned hm = half_max_u32(unsigned(u >> kKeyLow));
+        unsigned long long tie = __ballot(unsigned(u >> kKeyLow) == hm) & ((1ull << kSet) - 1ull);
+        if (__popcll(tie) > 1) {
+          const unsigned lm = half_max_u32(unsigned(u >> kKeyLow) == hm ? unsigned(u) & kKeyLowMask : 0u);
+          tie &= __ballot((unsigned(u) & kKeyLowMask) == lm);
+          if (__popcll(tie) > 1) {
+            const bool in = (tie >> lane) & 1ull;
+            const int im = wave_min_i32(in ? myidx : INT_MAX);
+            tie = __ballot(in && myidx == im);
+          }
+        }
+        const int slot = __builtin_ctzll(tie);
+        const long long g = lane_i64(gl, slot);
+        // (The first one has to beat the bound too: it may not when the best
+        // of all has no list, or too many share its float gain.)
+        if (step + np >= a.k || g < 0 || lane_u64(u, slot) <= bkey) break;
+        if (tid == 0) {
+          spt[np] = __builtin_amdgcn_readlane(myidx, slot);
+          spg[np] = g;
+        }
+        // The pick's hits, listed by the waves that hold its chunks.
+        if (nh > kHitCap - kHitPick) {
+          flush(nh);
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // its assignments come before later ones
+          nh = 0;
+        }
+#pragma unroll
+        for (int i = 0; i < kChunksPer; ++i) {
+          if (i * kListWaves + w >= nch) break;
+          if (mem[i] != slot) continue;                             // uniform
+          const int j = ej[i];
+          const float x = ec[i], bo = sball[j];
+          const bool ok = x < bo;
+          const unsigned long long mk = __ballot(ok);
+          if (ok) {
+            sball[j] = x;
+            shit[w][nh + __popcll(mk & ((1ull << lane) - 1ull))] =
+                uint4{unsigned(j) | (unsigned(np) << 16), __float_as_uint(x), __float_as_uint(bo),
+                      __float_as_uint(ev[i])};
+          }
+          nh += __popcll(mk);
+        }
+        done |= 1u << slot;
+        lds_barrier();
+        // The members' changes, from the entries whose best cost fell (the
+        // first chunks' best costs are read together).
+        float bn[kChunksPer];
+#pragma unroll
+        for (int i = 0; i < kChunksPer; ++i)
+          if (i < 4 || i * kListWaves + w < nch) bn[i] = sball[ej[i]];
+        // Few entries change in a chunk, so they are gathered first.
+        int nc = 0;
+        auto settle = [&]() {
+          const bool ok = lane < nc;
+          const uint4 h = schg[w][lane];
+          if (ok) {
+            const float cv = __uint_as_float(h.x), n1 = __uint_as_float(h.y), o1 = __uint_as_float(h.z);
+            atomicAdd(&sset[schm[w][lane]], (unsigned long long)fx_diff(fx_scale(double(__uint_as_float(h.w)), S),
+                                                                        fmaxf(n1 - cv, 0.f), o1 - cv));
+          }
+          nc = 0;
+        };
+#pragma unroll
+        for (int i = 0; i < kChunksPer; ++i) {
+          if (i * kListWaves + w >= nch) break;
+          const bool fell = bn[i] < eb[i];
+          const unsigned long long mk = __ballot(fell && ec[i] < eb[i]);
+          if (mk) {
+            const int m = __popcll(mk);
+            if (nc + m > 64) settle();
+            if ((mk >> lane) & 1ull) {
+              const int at = nc + __popcll(mk & ((1ull << lane) - 1ull));
+              schg[w][at] = uint4{__float_as_uint(ec[i]), __float_as_uint(bn[i]), __float_as_uint(eb[i]),
+                                  __float_as_uint(ev[i])};
+              schm[w][at] = mem[i];
+            }
+            nc += m;
+            eb[i] = fminf(eb[i], bn[i]);
+          }
+        }
+        if (nc) settle();
+        lds_barrier();
+      }
+      flush(nh);
+    }
+    if (np == 0) {
+      // The best candidate of all, alone, from its list or its row of T.
+      unsigned long long kb = 0ull;
+      int ib = INT_MAX, bb = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int b = lane + 64 * q;
+        const unsigned long long key = gain_key(word_gain(sgw[0][b]));
+        if (key > kb) {                                             // equal keys keep the lower block
+          kb = key;
+          bb = b;
+          ib = b * a.W + int(sgi[b] & 0xffu);
+        }
+      }
+      const unsigned long long top = wave_max_u64(kb);
+      if (top == 0ull) break;                                       // never with a candidate left
+      const int im = wave_min_i32(kb == top ? ib : INT_MAX);
+      const int wb = __builtin_amdgcn_readlane(bb, __builtin_ctzll(__ballot(kb == top && ib == im)));
+      const int t = min(im, a.n - 1);
+      const long long gb = word_gain(sgw[0][wb]);
+      const int len = __builtin_amdgcn_readfirstlane(int(sgl[wb]) & 0xfff);
+      const bool listed = len <= a.lcap;
+      lds_barrier();                                                // every wave has read the best costs
+      for (int e0 = w * 64; e0 < (listed ? len : a.n); e0 += kListBlock) {
+        const int e = e0 + lane;
+        int j = 0;
+        float x = __builtin_inff();
+        if (listed && e < len) {
+          const uint2 en = a.lists[size_t(t) * a.lstride + e];
+          j = min(int(en.x), a.n - 1);
+          x = __uint_as_float(en.y);
+        } else if (!listed && e < a.n) {
+          j = e;
+          x = a.T[size_t(t) * a.ldt + j];
+        }
+        const float bo = sball[j];
+        const bool ok = x < bo;
+        if (!__ballot(ok)) continue;
+        if (ok) {
+          sball[j] = x;
+          if (a.assign && unsigned(j - lo) < unsigned(cnt)) a.assign[j] = t;
+        }
+        apply_hits(ok, 0, j, x, bo, ok ? a.v[j] : 0.f);
+      }
+      if (tid == 0) {
+        spt[0] = t;
+        spg[0] = gb;
+      }
+      np = 1;
+      lds_barrier();
+    }
+    // The round's picks: chosen flags, and (block 0) the outputs.
+    if (w == 0) {
+      if (lane < np) {
+        const int t = spt[lane];
+        if (t >= lo && t < lo + cnt) ssel[t - lo] = 1;
       }
     }
     __syncthreads();
-    if (dobj != 0) atomicAdd(&sL, (unsigned long long)dobj);
-    obj_step = step;
-    // The chain candidates still ahead (slots above pos): their changes in
-    // the step, from the entries whose best cost fell, into LDS.
-#pragma unroll
-    for (int q = 0; q < kListSets; ++q) {
-      const int sl = q * kSlotsPerSet + half;
-      if (sl <= pos || sl > kListChain) continue;   // uniform over the wave
-      long long d = 0;
-      if (eok[q]) {
-        const float bn = sball[ej[q]], bo = eb[q];
-        if (bn < bo) {
-          const float cv = ec[q];
-          if (cv < bo) d = fx_diff(evs[q], fmaxf(bn - cv, 0.f), bo - cv);
-          eb[q] = bn;
-        }
+    if (step + np < a.k)
+      publish_list<NG>(sG, ssel, slen, cnt, srank, stop5, cand_slot(a.cand, (xc + 1) & 1, blk), epoch_of(xc + 1));
+    if (w == 1 && blk == 0) {
+      unsigned long long L = sL;
+      for (int i = 0; i < np; ++i) L += lane >= i ? sobj[i] : 0ull;
+      if (lane < np) {
+        a.selected[step + lane] = spt[lane];
+        if (a.step_gain) a.step_gain[step + lane] = fx_to_double(spg[lane], S);
+        if (a.step_obj) a.step_obj[step + lane] = fx_to_double((long long)L, S);
       }
-      if (__ballot(d != 0)) {
-        d = wave_sum_i64(d);
-        if (lane == 0) atomicAdd(&sacc[sl], (unsigned long long)d);
-      }
+      if (lane < kSet) sobj[lane] = 0ull;
+      if (lane == np - 1) sL = L;
     }
-    __syncthreads();
-    // Wave 0 folds the step's own changes.  A predicted next step starts
-    // without a barrier, so its hits add into the other parity's buffer
-    // while this one is read and cleared.
-    if (tid < 64) {
-      if (tid < cnt) sG[tid] += (long long)sdelta[par][tid];
-      sdelta[par][tid] = 0ull;
-    }
-    bool next = false;
-    if (pos < kListChain && step + 1 < a.k) {
-      int rn = -1;
-      long long gr = 0;
-      unsigned long long u = 0ull;
-#pragma unroll
-      for (int m = 1; m <= kListChain; ++m)
-        if (m == pos + 1) {
-          rn = rc[m];
-          gr = acc[m];
-          u = ub[m];
-        }
-      gr += (long long)sacc[pos + 1];
-      next = rn >= 0 && gr > 0 && (pack_key(fx_to_double(gr, S), rn) >> kIndexBits) > u;
-    }
-    // Wave 0 folded the gains itself, so it publishes without a barrier.
-    if (step + 1 < a.k && !next) publish_rows(sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc));
-    predicted = next;
-    pos += next ? 1 : 0;
+    step += np;
   }
-  __syncthreads();
-  if (blk == 0 && tid == 0 && obj_step >= 0 && a.step_obj) a.step_obj[obj_step] = fx_to_double((long long)sL, S);
 }
+
+template <int NG>
+__global__ __launch_bounds__(kListBlock) void sgs_list_kernel(IncDev a) { list_body<NG>(a, blockIdx.x, gridDim.x); }
 
 // The fixed-point scale of a scene (one block; the sum in the same order as
 // every block of the greedy would take it).
@@ -1699,6 +2024,7 @@ struct IncBatch {
   int g0[kMaxBatch + 1];
   IncDev scene[kMaxBatch];
 };
+static_assert(sizeof(IncBatch) <= 4096, "kernel arguments");
 
 __global__ __launch_bounds__(kBlock) void sgs_inc_batch_kernel(IncBatch b) {
   int s = 0;
@@ -1713,9 +2039,35 @@ __global__ __launch_bounds__(kBlock) void sgs_rows_batch_kernel(IncBatch b) {
   rows_body<NG, RL>(b.scene[s], int(blockIdx.x) - b.g0[s], b.g0[s + 1] - b.g0[s]);
 }
 
+template <int NG>
+__global__ __launch_bounds__(kBlock) void sgs_early_batch_kernel(IncBatch b) {
+  int s = 0;
+  while (s + 1 < b.count && int(blockIdx.x) >= b.g0[s + 1]) ++s;
+  early_body<NG>(b.scene[s], int(blockIdx.x) - b.g0[s], b.g0[s + 1] - b.g0[s]);
+}
+
+// Scenes without a list phase (k_begin = k) leave at once.
+template <int NG>
+__global__ __launch_bounds__(kListBlock) void sgs_list_batch_kernel(IncBatch b) {
+  int s = 0;
+  while (s + 1 < b.count && int(blockIdx.x) >= b.g0[s + 1]) ++s;
+  list_body<NG>(b.scene[s], int(blockIdx.x) - b.g0[s], b.g0[s + 1] - b.g0[s]);
+}
+
 // The rows form runs when the scene's best costs fit in LDS and a block has
 // at most two columns per lane; otherwise the exchange form.
 bool use_rows(int64_t n, int W) { return n <= kRowsMaxN && W <= kRowsMaxW; }
+
+// Blocks of a scene's greedy, and whether it is the rows form.  The rows form
+// takes one block per kRowsPer tokens (up to one per compute unit: the early
+// steps and the hits' row segments spread over more of the chip, 4096 tokens
+// 0.05 ms faster than with one per 32), the exchange form one per 64.
+constexpr int kRowsPer = 16;
+int inc_blocks(int64_t n, int cus, bool compact, bool* rows) {
+  const int nb = blocks_for(n, cus, kRowsPer);
+  *rows = !compact && use_rows(n, int((n + nb - 1) / nb));
+  return *rows ? nb : blocks_for(n, cus, 64);
+}
 
 // The instance for the largest n and W of a launch.
 constexpr int kRowsSmallN = kRowChunk * kWaves * 8;
@@ -1732,11 +2084,19 @@ const void* rows_batch_kernel(int64_t n, int W) {
   return reinterpret_cast<const void*>(sgs_rows_batch_kernel<2, 16>);
 }
 
+// The step from which a scene's lists serve, and whether they do (there have
+// to be some steps left to pay for building them).  A step of the rows kernel
+// takes 7 us, one of the list kernel 1.5; but lists built too early are long
+// (n / 320: four scenes of 6272 tokens 4.0 ms instead of 2.6; n / 192: level).
+int list_step(int64_t n) { return int(std::max<int64_t>(8, std::min<int64_t>(128, n / 128))); }
+bool lists_for(int64_t n, int64_t k, int W) { return n <= kListMaxN && W <= kRowsMaxW && k > list_step(n) + 8; }
+
 // Exchange slots and lists, the first pass's partial gains and scale, then
 // (when the rows form may run) T.
 constexpr int kPassParts = 3;   // row ranges of the first pass (three blocks per compute unit fit at once)
+constexpr int kListOwnK = 128;  // up to this many picks the lists take the place of the rows of T
 struct IncLayout {
-  size_t part, scale, T, epart, lists, ho_gain, ho_sel, ho_b, misc, total;
+  size_t part, scale, T, epart, epart_bytes, lists, ho_gain, ho_sel, ho_b, misc, total;
 };
 IncLayout inc_layout(int64_t n, int64_t k, bool compact) {
   IncLayout L;
@@ -1745,30 +2105,30 @@ IncLayout inc_layout(int64_t n, int64_t k, bool compact) {
   L.scale = o; o += 256;
   L.T = o;
   if (!compact && n <= kRowsMaxN) o += a256(size_t(n) * rows_ldt(n) * sizeof(float));
-  // The early kernel's partial sums (rows schedule, n <= kEarlyMaxN), for
-  // as many blocks as the scene can have.
+  // The early kernel's partial sums (rows schedule, n <= kEarlyMaxN): one
+  // row per 64 tokens, and more in the lists' memory, which is free until the
+  // lists are built.
   L.epart = o;
+  L.epart_bytes = 0;
   const bool early = !compact && n <= kEarlyMaxN;
   if (early) o += a256(size_t(std::min<int64_t>(kMaxBlocks, (n + 63) / 64)) * early_ldp(n) * 8);
-  // The candidate lists (n <= kListMaxN, more than kListStep picks) and the
-  // hand-over between launches (lists or the early kernel).
+  // The candidate lists (n <= kListMaxN), and the hand-over between launches.
   L.lists = L.ho_gain = L.ho_sel = L.ho_b = L.misc = o;
-  const bool lists = !compact && n <= kListMaxN && k > kListStep;
-  if (lists) {
-    L.lists = o;   o += a256(size_t(n) * kListSlots * 16);
-  }
-  if (lists || early) {
+  if (early) {
+    L.lists = o;
+    if (k > kListOwnK) o += a256(size_t(n) * kListCap * sizeof(uint2));
+    L.epart_bytes = o - L.epart;
     L.ho_gain = o; o += a256(size_t(n) * 8);
     L.ho_sel = o;  o += a256(size_t(n));
     L.ho_b = o;    o += a256(size_t(rows_ldt(n)) * 4);
-    L.misc = o;    o += a256(24 + 4 + size_t(kMaxBlocks) * 4);   // objective, exchanges, next step; lfail; lblock
+    L.misc = o;    o += a256(24 + 4 + size_t(kMaxBlocks) * 4);   // objective, (unused), next step
   }
   L.total = o;
   return L;
 }
 size_t inc_bytes(int64_t n, int64_t k, bool compact) { return inc_layout(n, k, compact).total; }
 
-IncDev inc_dev(const SgsParams& p, char* w, int W, bool rows) {
+IncDev inc_dev(const SgsParams& p, char* w, int nb, int W, bool rows) {
   const Layout L = layout(p.n, p.k);
   IncDev a{};
   a.C = p.cost;
@@ -1797,21 +2157,26 @@ IncDev inc_dev(const SgsParams& p, char* w, int W, bool rows) {
   a.scale = reinterpret_cast<const int*>(w + M.scale);
   a.k_begin = 0;
   a.k_end = p.k;
-  a.gate = nullptr;
-  a.gate_val = 0u;
-  const bool lists = rows && lists_for(p.n, p.k, W);
-  const bool early = rows && early_for(p.n, W);
-  const bool ho = lists || early;
-  a.lists = lists ? reinterpret_cast<unsigned long long*>(w + M.lists) : nullptr;
-  a.ho_gain = ho ? reinterpret_cast<long long*>(w + M.ho_gain) : nullptr;
-  a.ho_sel = ho ? reinterpret_cast<unsigned char*>(w + M.ho_sel) : nullptr;
-  a.ho_b = ho ? reinterpret_cast<float*>(w + M.ho_b) : nullptr;
-  a.ho_misc = ho ? reinterpret_cast<long long*>(w + M.misc) : nullptr;
-  a.lfail = lists ? reinterpret_cast<unsigned int*>(w + M.misc + 24) : nullptr;
-  a.lblock = lists ? reinterpret_cast<unsigned int*>(w + M.misc + 28) : nullptr;
-  a.epart = early ? reinterpret_cast<long long*>(w + M.epart) : nullptr;
-  a.ldp = early ? early_ldp(p.n) : 0;
-  a.start = nullptr;
+  if (rows && early_for(p.n, W)) {
+    a.ho_gain = reinterpret_cast<long long*>(w + M.ho_gain);
+    a.ho_sel = reinterpret_cast<unsigned char*>(w + M.ho_sel);
+    a.ho_b = reinterpret_cast<float*>(w + M.ho_b);
+    a.ho_misc = reinterpret_cast<long long*>(w + M.misc);
+    a.epart = reinterpret_cast<long long*>(w + M.epart);
+    a.ldp = early_ldp(p.n);
+    a.eshares = int(std::min<size_t>(nb, M.epart_bytes / (size_t(a.ldp) * 8)));
+  }
+  if (rows && lists_for(p.n, p.k, W)) {
+    // Lists of their own, or (small budgets) at the start of the rows of T
+    // that they replace.
+    const bool own = p.k > kListOwnK;
+    a.lists = own ? reinterpret_cast<uint2*>(w + M.lists) : reinterpret_cast<uint2*>(a.T);
+    a.lcap = own ? kListCap : std::min(kListCap, a.ldt / 2);
+    a.lstride = own ? size_t(kListCap) : size_t(a.ldt) / 2;
+    a.lent = list_ent(p.n, W);
+    a.llen = reinterpret_cast<unsigned int*>(w + L.list);   // the compact form's change lists are not in use
+    a.k_end = list_step(p.n);
+  }
   return a;
 }
 
@@ -1831,9 +2196,9 @@ hipError_t launch_first_pass(const IncDev& a, int nb, hipStream_t stream) {
 size_t lds_for(int W) { return size_t(W) * (8 + 4 + 4 + 1) + 16; }
 size_t lds_rows(int W, int64_t n) { return size_t((W + 1) & ~1) * 8 + size_t(rows_ldt(n)) * 4 + size_t(W) + 16; }
 
-hipError_t fits(const void* kernel, size_t lds) {
+hipError_t fits(const void* kernel, size_t lds, int threads = kBlock) {
   int per_cu = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, lds);
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds);
   if (e != hipSuccess) return e;
   return per_cu < 1 ? hipErrorCooperativeLaunchTooLarge : hipSuccess;
 }
@@ -1845,6 +2210,14 @@ int device_cus(int* cus) {
   return hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
 }
 
+// The instances for W columns a block.
+const void* early_kernel(int W) {
+  return W <= 64 ? reinterpret_cast<const void*>(sgs_early_kernel<1>) : reinterpret_cast<const void*>(sgs_early_kernel<2>);
+}
+const void* list_kernel(int W) {
+  return W <= 64 ? reinterpret_cast<const void*>(sgs_list_kernel<1>) : reinterpret_cast<const void*>(sgs_list_kernel<2>);
+}
+
 // The greedy's launches; with `fused` the step-0 gains and T were written by
 // fst_epilogue_sgs_kernel (and the scale before it), so the first pass is
 // skipped and the gains come from its partial sums.
@@ -1852,38 +2225,31 @@ hipError_t run_incremental(const SgsParams& p, bool compact, const SgsFused* fus
   int cus = 0;
   hipError_t e = hipError_t(device_cus(&cus));
   if (e != hipSuccess) return e;
-  const int nb = blocks_for(p.n, cus);
+  bool rows = false;
+  const int nb = inc_blocks(p.n, cus, compact, &rows);
   const int W = (p.n + nb - 1) / nb;
-  const bool rows = !compact && use_rows(p.n, W);
   if (fused && !rows) return hipErrorInvalidValue;
   const void* kernel = rows ? rows_kernel(p.n, W) : reinterpret_cast<const void*>(sgs_inc_kernel);
   const size_t lds = rows ? lds_rows(W, p.n) : lds_for(W);
   if ((e = fits(kernel, lds)) != hipSuccess) return e;
 
-  IncDev a = inc_dev(p, static_cast<char*>(p.workspace), W, rows);
+  IncDev a = inc_dev(p, static_cast<char*>(p.workspace), nb, W, rows);
   if (fused) {
     a.part = fused->part;
     a.P = fused->P;
   }
-  // Scenes the list phase serves: the rows kernel stops after kListStep
-  // steps, the lists are built, and the list kernel (or, when the lists do
-  // not fit, the rows kernel again) runs the rest.
-  const bool lists = a.lists != nullptr;
-  if (lists) {
-    a.k_end = kListStep;
-    if ((e = fits(reinterpret_cast<const void*>(sgs_list_kernel), list_lds(p.n))) != hipSuccess) return e;
-  }
-  // The early kernel runs the first steps, while they improve many targets;
-  // the rows kernel continues from the step it stopped before.
-  const bool early = a.epart != nullptr;
-  if (early && (e = fits(reinterpret_cast<const void*>(sgs_early_kernel), lds)) != hipSuccess) return e;
+  // The early kernel runs the first steps, while they improve many targets,
+  // the rows kernel those up to the list phase (or the end), the list kernel
+  // the rest.
+  const bool early = a.epart != nullptr, lists = a.lists != nullptr;
+  if (early && (e = fits(early_kernel(W), lds)) != hipSuccess) return e;
+  if (lists && (e = fits(list_kernel(W), kListLds, kListBlock)) != hipSuccess) return e;
   sgs_inc_init_kernel<<<std::min(1024, (std::max(p.n, p.k) + 255) / 256), 256, 0, stream>>>(a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!fused && (e = launch_first_pass(a, nb, stream)) != hipSuccess) return e;
   if (early) {
     void* eargs[] = {&a};
-    if ((e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(sgs_early_kernel), dim3(nb), dim3(kBlock), eargs,
-                                        lds, stream)) != hipSuccess)
+    if ((e = hipLaunchCooperativeKernel(early_kernel(W), dim3(nb), dim3(kBlock), eargs, lds, stream)) != hipSuccess)
       return e;
     a.start = a.ho_misc + 2;
   }
@@ -1892,19 +2258,9 @@ hipError_t run_incremental(const SgsParams& p, bool compact, const SgsFused* fus
   if (lists) {
     list_build_kernel<<<(p.n + 3) / 4, 256, 0, stream>>>(a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    IncDev b = a;
-    b.start = nullptr;
-    b.k_begin = kListStep;
-    b.k_end = p.k;
-    void* bargs[] = {&b};
-    if ((e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(sgs_list_kernel), dim3(nb), dim3(kBlock), bargs,
-                                        list_lds(p.n), stream)) != hipSuccess)
+    a.k_begin = a.k_end;
+    if ((e = hipLaunchCooperativeKernel(list_kernel(W), dim3(nb), dim3(kListBlock), args, kListLds, stream)) != hipSuccess)
       return e;
-    IncDev c = b;
-    c.gate = a.lfail;
-    c.gate_val = 1u;
-    void* cargs[] = {&c};
-    if ((e = hipLaunchCooperativeKernel(kernel, dim3(nb), dim3(kBlock), cargs, lds, stream)) != hipSuccess) return e;
   }
   return launch_mark_aborted(a.abort, a.selected, a.k, stream);
 }
@@ -1922,8 +2278,9 @@ hipError_t launch_sgs_incremental(const SgsParams& p, bool compact, hipStream_t 
 bool sgs_fused_fits(int64_t n) {
   int cus = 0;
   if (device_cus(&cus) != hipSuccess || n < 64 || n % 64 != 0) return false;
-  const int nb = blocks_for(n, cus);
-  return use_rows(n, int((n + nb - 1) / nb));
+  bool rows = false;
+  inc_blocks(n, cus, false, &rows);
+  return rows;
 }
 
 size_t sgs_fused_workspace_bytes(int64_t n, int64_t k) {
@@ -1934,8 +2291,9 @@ hipError_t sgs_fused_prepare(const SgsParams& p, SgsFused* f, hipStream_t stream
   int cus = 0;
   hipError_t e = hipError_t(device_cus(&cus));
   if (e != hipSuccess) return e;
-  const int nb = blocks_for(p.n, cus);
-  IncDev a = inc_dev(p, static_cast<char*>(p.workspace), (p.n + nb - 1) / nb, true);
+  bool rows = false;
+  const int nb = inc_blocks(p.n, cus, false, &rows);
+  IncDev a = inc_dev(p, static_cast<char*>(p.workspace), nb, (p.n + nb - 1) / nb, true);
   f->T = a.T;
   f->ldt = a.ldt;
   f->part = reinterpret_cast<long long*>(static_cast<char*>(p.workspace) + inc_bytes(p.n, p.k, false));
@@ -1970,7 +2328,7 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
   int used = count;
   for (int s = 0; s < count; ++s) {
     nb[s] = 1;
-    cap[s] = blocks_for(p[s].n, cus);
+    cap[s] = blocks_for(p[s].n, cus, compact ? 64 : kRowsPer);
   }
   while (used < cus) {
     int best = -1;
@@ -1987,15 +2345,20 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
     ++nb[best];
     ++used;
   }
-  // The rows form when every scene allows it (one form per launch).
-  bool rows = !compact;
+  // The rows form when every scene allows it (one form per launch), with the
+  // early and the list kernel when they serve every scene.
+  bool rows = !compact, early = !compact, lists = false;
   int wmax = 0, nmax = 0;
   for (int s = 0; s < count; ++s) {
     const int W = (p[s].n + nb[s] - 1) / nb[s];
     rows = rows && use_rows(p[s].n, W);
+    early = early && early_for(p[s].n, W);
+    lists = lists || lists_for(p[s].n, p[s].k, W);
     wmax = std::max(wmax, W);
     nmax = std::max(nmax, p[s].n);
   }
+  early = early && rows;
+  lists = lists && early;
   IncBatch b{};
   b.count = count;
   b.g0[0] = 0;
@@ -2003,20 +2366,48 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
   char* w = static_cast<char*>(workspace);
   for (int s = 0; s < count; ++s) {
     const int W = (p[s].n + nb[s] - 1) / nb[s];
-    b.scene[s] = inc_dev(p[s], w + off, W, rows);
+    IncDev& a = b.scene[s];
+    a = inc_dev(p[s], w + off, nb[s], W, rows);
+    if (!early) {
+      a.epart = nullptr;
+      a.lists = nullptr;
+      a.k_end = a.k;
+    }
     b.g0[s + 1] = b.g0[s] + nb[s];
     lds = std::max(lds, rows ? lds_rows(W, p[s].n) : lds_for(W));
     off += inc_bytes(p[s].n, p[s].k, compact);
   }
+  const bool one = wmax <= 64;   // one column group per block
   const void* kernel = rows ? rows_batch_kernel(nmax, wmax) : reinterpret_cast<const void*>(sgs_inc_batch_kernel);
+  const void* ekernel = one ? reinterpret_cast<const void*>(sgs_early_batch_kernel<1>)
+                            : reinterpret_cast<const void*>(sgs_early_batch_kernel<2>);
+  const void* lkernel = one ? reinterpret_cast<const void*>(sgs_list_batch_kernel<1>)
+                            : reinterpret_cast<const void*>(sgs_list_batch_kernel<2>);
   if ((e = fits(kernel, lds)) != hipSuccess) return e;
+  if (early && (e = fits(ekernel, lds)) != hipSuccess) return e;
+  if (lists && (e = fits(lkernel, kListLds, kListBlock)) != hipSuccess) return e;
   for (int s = 0; s < count; ++s) {
     sgs_inc_init_kernel<<<std::min(1024, (std::max(p[s].n, p[s].k) + 255) / 256), 256, 0, stream>>>(b.scene[s]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = launch_first_pass(b.scene[s], b.g0[s + 1] - b.g0[s], stream)) != hipSuccess) return e;
   }
   void* args[] = {&b};
+  if (early) {
+    if ((e = hipLaunchCooperativeKernel(ekernel, dim3(used), dim3(kBlock), args, lds, stream)) != hipSuccess) return e;
+    for (int s = 0; s < count; ++s) b.scene[s].start = b.scene[s].ho_misc + 2;
+  }
   if ((e = hipLaunchCooperativeKernel(kernel, dim3(used), dim3(kBlock), args, lds, stream)) != hipSuccess) return e;
+  if (lists) {
+    for (int s = 0; s < count; ++s) {
+      IncDev& a = b.scene[s];
+      a.k_begin = a.k_end;
+      if (!a.lists) continue;
+      list_build_kernel<<<(p[s].n + 3) / 4, 256, 0, stream>>>(a);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if ((e = hipLaunchCooperativeKernel(lkernel, dim3(used), dim3(kListBlock), args, kListLds, stream)) != hipSuccess)
+      return e;
+  }
   for (int s = 0; s < count; ++s)
     if ((e = launch_mark_aborted(b.scene[s].abort, b.scene[s].selected, b.scene[s].k, stream)) != hipSuccess) return e;
   return hipSuccess;

@@ -89,7 +89,6 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
   __shared__ long long red[kBlock];
   __shared__ long long sg[kWaves];
   __shared__ double sd[kWaves];
-  __shared__ int si[kWaves];
   __shared__ unsigned long long su[kWaves];
   __shared__ int sflag;
   __shared__ long long sLw[kWaves];            // this block's objective part, one running share per wave
@@ -191,7 +190,7 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
 
   __syncthreads();
   local_gains();
-  publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), sg, si);
+  publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), su);
 
   const int nch = a.ldt / kChunkT;
   for (int step = 0; step < a.k; ++step) {
@@ -252,7 +251,7 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
     if (step + 1 < a.k) {
       local_gains();
       publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, (step + 1) & 1, blk),
-                     epoch_of(step + 1), sg, si);
+                     epoch_of(step + 1), su);
     }
   }
 }
@@ -290,7 +289,7 @@ hipError_t launch_sgs_local(const SgsParams& p, const int32_t* nbr, int g, hipSt
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-  const int nb = blocks_for(p.n, cus);
+  const int nb = blocks_for(p.n, cus, 64);
   const int W = (p.n + nb - 1) / nb;
   const int ldt = local_ldt(p.n);
   const size_t lds = size_t((W + 1) & ~1) * 8 + size_t(ldt) * 4 + size_t(W) * g * (4 + 4 + 2) + size_t(W) * (4 + 1) + 16;

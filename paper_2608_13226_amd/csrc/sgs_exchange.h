@@ -37,6 +37,9 @@ constexpr int kIndexBits = 20;     // candidate: [epoch | 43-bit gain | 20-bit i
 constexpr unsigned long long kIndexMask = (1ull << kIndexBits) - 1ull;
 constexpr unsigned long long kEpoch = 1ull << 63;
 constexpr unsigned long long kNoCandidate = 1ull;   // below every real candidate
+// The list kernel's words hold exact gains (62 bits); bit 62 marks "none".
+constexpr unsigned long long kNoGain = 1ull << 62;
+constexpr int kListWord = 8;                        // first of a slot's words that the list kernel uses
 // Every wait in the kernel is bounded (give_up in common.h): a wait that
 // gives up raises the abort flag, every block leaves its waits and returns,
 // and a kernel after the launch fills selected[] with -1.
@@ -63,24 +66,23 @@ struct IncDev {
   const long long* part;      // incremental form: [P][n] step-0 gains summed over P row ranges
   int P;
   const int* scale;           // incremental form: the fixed-point exponent S
-  // Rows schedule in two launches with a hand-over (see k_sgs_inc.hip): the
-  // steps of this launch, the word that decides whether it runs, and the
-  // state handed from one launch to the next.
+  // Rows schedule in several launches with a hand-over (see k_sgs_inc.hip):
+  // the steps of this launch and the state handed from one to the next.
   int k_begin, k_end;         // steps [k_begin, k_end); [0, k) for a single launch
-  const unsigned int* gate;   // the launch runs only if *gate == gate_val (null: always)
-  unsigned int gate_val;
   long long* ho_gain;         // [n] running gains
   unsigned char* ho_sel;      // [n] chosen flags
   float* ho_b;                // [ldt] best costs
   long long* ho_misc;         // [0] objective in fixed point, [1] exchanges so far, [2] next step
-  unsigned long long* lists;  // [n][kListSlots][2] candidate lists
-  unsigned int* lfail;        // the lists do not fit
-  unsigned int* lblock;       // [blocks] pairs of each block's candidates
+  uint2* lists;               // candidate c's list at lists + c lstride: (target, cost) pairs
+  size_t lstride;
+  int lcap;                   // pairs a list holds; a candidate with more keeps its row of T
+  int lent;                   // pairs of its own candidates that a block holds
+  unsigned int* llen;         // [n] pairs of each candidate
   // Early steps of the rows schedule (sgs_early_kernel): each block's partial
   // gain changes of every column, and the step a launch after it starts from
   // (null: k_begin).
-  long long* epart;           // [blocks][ldp]: columns 0 .. n - 1, then the objective's change
-  int ldp;
+  long long* epart;           // [eshares][ldp]: columns 0 .. n - 1, then the objective's change
+  int ldp, eshares;
   const long long* start;
 };
 
@@ -99,8 +101,9 @@ struct Layout {
 
 size_t a256(size_t x) { return (x + 255) / 256 * 256; }
 
-int blocks_for(int64_t n, int cus) {
-  return int(std::max<int64_t>(1, std::min<int64_t>(std::min(cus, kMaxBlocks), (n + 63) / 64)));
+// One block per `per` tokens, at most one per compute unit.
+int blocks_for(int64_t n, int cus, int per) {
+  return int(std::max<int64_t>(1, std::min<int64_t>(std::min(cus, kMaxBlocks), (n + per - 1) / per)));
 }
 
 // Sized for the largest grid (kMaxBlocks blocks of W = ceil(n / blocks) rows).
@@ -126,11 +129,23 @@ __host__ __device__ __forceinline__ unsigned long long* lens_slot(unsigned long 
 }
 
 // Nonnegative gain truncated to its top 43 bits (relative resolution 2^-31),
-// then the inverted index: larger gain first, then smaller index.  Indices
-// are below 2^18, so every real candidate exceeds kNoCandidate.
+// then the inverted index: larger gain first, then smaller index.  Every
+// comparison of candidates goes by this key, inside a block as across blocks,
+// so the picks do not depend on how the columns are split over the blocks.
+// Indices are below 2^18, so every real candidate exceeds kNoCandidate.
 __device__ __forceinline__ unsigned long long pack_key(double g, int idx) {
   const unsigned long long gb = (unsigned long long)__double_as_longlong(g) >> (kIndexBits + 1);
   return (gb << kIndexBits) | (kIndexMask - (unsigned long long)idx);
+}
+
+// The key's order for an exact gain (-1: none, below all): the top 43 bits
+// of its float64 value, which scaling by 2^-S does not change, plus one.
+__device__ __forceinline__ unsigned long long gain_key(long long g) {
+  return g < 0 ? 0ull : ((unsigned long long)__double_as_longlong(double(g)) >> (kIndexBits + 1)) + 1ull;
+}
+__device__ __forceinline__ unsigned long long gain_word(long long g) { return g < 0 ? kNoGain : (unsigned long long)g; }
+__device__ __forceinline__ long long word_gain(unsigned long long x) {
+  return (x & kNoGain) ? -1ll : (long long)(x & ~kEpoch);
 }
 
 // Epoch bit of the candidates of exchange l (the step, unless steps skip
@@ -144,19 +159,13 @@ __global__ void sgs_inc_init_kernel(IncDev a) {
   const int gt = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
   for (int s = gt; s < kMaxBlocks; s += nt) {
     a.lens[size_t(s) * kSlotStride] = 0ull;
-    // Word 0 of a candidate slot holds the key; the rows schedule also
-    // writes word 1 (the second key).
-    for (int w = 0; w < 2; ++w) {
+    for (int w = 0; w < kSlotStride; ++w) {
       a.cand[size_t(s) * kSlotStride + w] = 0ull;
       a.cand[size_t(kMaxBlocks + s) * kSlotStride + w] = 0ull;
     }
   }
   for (int j = gt; j < a.n; j += nt)
     if (a.assign) a.assign[j] = -1;
-  if (a.lfail) {
-    for (int s = gt; s < kMaxBlocks; s += nt) a.lblock[s] = 0u;
-    if (gt == 0) *a.lfail = 0u;
-  }
   if (gt == 0) *a.abort = a.abort_init;
 }
 
@@ -180,6 +189,32 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned x) {
   x = max(x, unsigned(__builtin_amdgcn_mov_dpp(int(x), kDppSteps[3], 0xf, 0xf, false)));
   return max(max(unsigned(__builtin_amdgcn_readlane(int(x), 0)), unsigned(__builtin_amdgcn_readlane(int(x), 16))),
              max(unsigned(__builtin_amdgcn_readlane(int(x), 32)), unsigned(__builtin_amdgcn_readlane(int(x), 48))));
+}
+
+// The maximum over lanes 0 .. 31, in every lane.
+__device__ __forceinline__ unsigned half_max_u32(unsigned x) {
+  x = max(x, unsigned(__builtin_amdgcn_mov_dpp(int(x), kDppSteps[0], 0xf, 0xf, false)));
+  x = max(x, unsigned(__builtin_amdgcn_mov_dpp(int(x), kDppSteps[1], 0xf, 0xf, false)));
+  x = max(x, unsigned(__builtin_amdgcn_mov_dpp(int(x), kDppSteps[2], 0xf, 0xf, false)));
+  x = max(x, unsigned(__builtin_amdgcn_mov_dpp(int(x), kDppSteps[3], 0xf, 0xf, false)));
+  return max(unsigned(__builtin_amdgcn_readlane(int(x), 0)), unsigned(__builtin_amdgcn_readlane(int(x), 16)));
+}
+
+__device__ __forceinline__ int wave_sum_i32(int x) {
+  x += __builtin_amdgcn_mov_dpp(x, kDppSteps[0], 0xf, 0xf, false);
+  x += __builtin_amdgcn_mov_dpp(x, kDppSteps[1], 0xf, 0xf, false);
+  x += __builtin_amdgcn_mov_dpp(x, kDppSteps[2], 0xf, 0xf, false);
+  x += __builtin_amdgcn_mov_dpp(x, kDppSteps[3], 0xf, 0xf, false);
+  return __builtin_amdgcn_readlane(x, 0) + __builtin_amdgcn_readlane(x, 16) + __builtin_amdgcn_readlane(x, 32) +
+         __builtin_amdgcn_readlane(x, 48);
+}
+
+// A workgroup barrier that orders LDS only: outstanding global loads stay in
+// flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // The 64-bit maximum as 32-bit ones: the largest high word, then the low
@@ -338,58 +373,32 @@ __device__ double block_max_all(double x, double* sd) {
   return s;
 }
 
-// Argmax of (g, gi) over a whole wave (every lane active), in every lane:
-// the largest gain, then the smallest index among the lanes that hold it.
-// g = -1 marks no candidate (gi = INT_MAX).
-__device__ __forceinline__ void wave_argmax(long long& g, int& gi) {
-  const long long top = wave_max_i64(g);
-  gi = wave_min_i32(g == top ? gi : INT_MAX);
-  g = top;
+// The block's best unchosen column by key, published as its candidate for
+// the step.  With at most 64 columns wave 0 does it alone, one column per
+// lane, and no barrier follows: the callers' next step begins with one
+// (read_winner), and the gains and chosen flags it reads were last written by
+// wave 0 itself.
+__device__ __forceinline__ unsigned long long column_key(const long long* sG, const unsigned char* ssel, int lo, int i,
+                                                         int cnt, int S) {
+  return i < cnt && !ssel[i] ? pack_key(fx_to_double(sG[i], S), lo + i) : kNoCandidate;
 }
-
-// Exact argmax (ties to the smaller index) of the block's unchosen columns,
-// published as the block's candidate for the step; across blocks the gains
-// compare as doubles truncated to 43 bits.  With at most 64 columns wave 0
-// does it alone, one column per lane, and no barrier follows: the callers'
-// next step begins with one (read_winner), and the gains and chosen flags it
-// reads were last written by wave 0 itself.
 __device__ __forceinline__ void publish_argmax(const long long* sG, const unsigned char* ssel, int lo, int cnt,
                                                int S, unsigned long long* slot, unsigned long long epoch,
-                                               long long* sg, int* si) {
+                                               unsigned long long* su) {
   if (cnt <= 64) {
     if (threadIdx.x >= 64) return;
-    const int i = threadIdx.x;
-    long long g = -1;
-    int gi = INT_MAX;
-    if (i < cnt && !ssel[i]) {
-      g = sG[i];
-      gi = lo + i;
-    }
-    wave_argmax(g, gi);
-    if (i == 0) put(slot, (gi != INT_MAX ? pack_key(fx_to_double(g, S), gi) : kNoCandidate) | epoch);
+    const unsigned long long key = wave_max_u64(column_key(sG, ssel, lo, threadIdx.x, cnt, S));
+    if (threadIdx.x == 0) put(slot, key | epoch);
     return;
   }
-  long long g = -1;
-  int gi = INT_MAX;
-  for (int i = threadIdx.x; i < cnt; i += kBlock)
-    if (!ssel[i] && sG[i] > g) {   // increasing i: ties keep the smaller index
-      g = sG[i];
-      gi = lo + i;
-    }
-  wave_argmax(g, gi);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane == 0) {
-    sg[w] = g;
-    si[w] = gi;
-  }
+  unsigned long long key = kNoCandidate;
+  for (int i = threadIdx.x; i < cnt; i += kBlock) key = max(key, column_key(sG, ssel, lo, i, cnt, S));
+  key = wave_max_u64(key);
+  if ((threadIdx.x & 63) == 0) su[threadIdx.x >> 6] = key;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int q = 1; q < kWaves; ++q)
-      if (sg[q] > g || (sg[q] == g && si[q] < gi)) {
-        g = sg[q];
-        gi = si[q];
-      }
-    put(slot, (gi != INT_MAX ? pack_key(fx_to_double(g, S), gi) : kNoCandidate) | epoch);
+    for (int q = 1; q < kWaves; ++q) key = max(key, su[q]);
+    put(slot, key | epoch);
   }
   __syncthreads();
 }

@@ -39,8 +39,9 @@
  *   - Results are bitwise reproducible run to run on the same GPU.  Calls on
  *     distinct workspaces and streams may run concurrently.
  *   - Waits between the blocks of one launch are bounded.  The greedy
- *     selection calls (sgs_select, sgs_select_batch, sgs_local_select, and the
- *     greedy of prune) run persistent launches whose blocks wait for each
+ *     selection calls (sgs_select, sgs_select_batch, sgs_local_select, the
+ *     greedy of prune, and sgs_literal_select up to n = 2048 and k = 256
+ *     without a trajectory to follow) run persistent launches whose blocks wait for each
  *     other (lite_select has no such waits: ordinary launches only).  A wait
  *     that has polled for about a second (far beyond any legitimate wait: a launch
  *     starved of compute units, or a broken device) gives up, every block of
@@ -396,7 +397,9 @@ cp_status coverprune_sgs_local_select(const float* cost, int64_t n, const float*
  * sums in a fixed order (deterministic); E underflows to 0 where
  * C / epsilon exceeds about 708, so epsilon should stay above max C / 700.
  * Each step costs `rounds` passes over an n x l matrix and one pass over the
- * cost.
+ * cost: separate launches, or, for n <= 2048 and k <= 256 without `follow` on
+ * a stream that is not being captured, one persistent launch that keeps both
+ * on the compute units.
  *
  *   cost, n, capacity: as for coverprune_sgs_select (every retained token must
  *             reach some target at finite E, e.g. C(s, s) = 0 as the FST cost has)
@@ -411,7 +414,8 @@ cp_status coverprune_sgs_local_select(const float* cost, int64_t n, const float*
  *   step_residual  [k] double output (may be NULL): sum_j r_j before each pick
  *   objective      [1] double output (may be NULL): <P, C_S> of the final plan
  * With `follow` set and both step outputs NULL only the final plan is solved.
- * Workspace: about 8 k + 40 bytes per token plus 8 k per 64 tokens.
+ * Workspace: about 8 k + 40 bytes per token plus 8 k per 64 tokens; for
+ * n <= 2048 and k <= 256 at least n^2 bytes plus 260 KB.
  */
 #define CP_SGS_LITERAL_MAX_K 4096
 #define CP_SGS_LITERAL_MAX_ROUNDS 1000000

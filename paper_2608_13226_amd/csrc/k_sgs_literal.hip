@@ -29,13 +29,13 @@
 //   lit_select_kernel   one block: panel sums in panel order, argmin over the
 //                       unselected tokens, residual mass
 // Every sum is float64 in a fixed order, so results are deterministic.
+// Small scenes run in one persistent launch instead (lit_persistent_kernel).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cfloat>
 
-#include "common.h"
-#include "launch.h"
+#include "sgs_exchange.h"
 
 namespace cp {
 namespace {
@@ -257,7 +257,415 @@ __global__ void lit_objective_sum_kernel(LitDev p) {
   }
 }
 
-size_t a256(size_t x) { return (x + 255) / 256 * 256; }
+// ---------------------------------------------------------------------------
+// The same greedy in one cooperative launch, for scenes whose E fits in
+// registers and whose cost in LDS (n <= kPersN, k <= kPersK; no trajectory to follow).
+//
+// A scaling round is two dependent passes over a small matrix (3.4 MB at
+// n = 2048, k = 205), and 10 250 rounds follow one another: as two launches a
+// round they took 18 us, nearly all of it launching and filling the pipeline.
+// Here ceil(n / 64) solver blocks keep 64 rows of E each in registers (wave w
+// rows 8 w .. 8 w + 7, lane and chunk the column) for the whole call.  Per
+// round a solver forms t_j and b_j of its rows, its column sums, and publishes
+// them; every solver then adds all blocks' sums in block order and holds the
+// same a_i.  A column sum is nonnegative, so its sign bit carries the epoch of
+// the exchange: one trip through memory a round, no flags and no grid barrier.
+// After the last round the residuals go to the scoring blocks (ceil(n / 8),
+// each with 8 rows of the cost in LDS), which write their partial scores;
+// block b adds the partials of candidates 8 b .. 8 b + 7, publishes its best
+// one, and every block takes the same pick.  Bound by the exchange (about
+// 2 us a round) and the chain of sums, divisions and barriers around it (as
+// long again); n = 2048, k = 205, 50 rounds: 177 ms as launches, 46 ms here.
+constexpr int kPersN = 2048;
+constexpr int kPersK = 256;
+constexpr int kPersRows = 64;                         // rows of E a solver block holds
+constexpr int kPersSolvers = kPersN / kPersRows;      // 32
+constexpr int kPersScore = 8;                         // rows of the cost a block holds, and candidates it adds up
+constexpr int kPersBlocks = kPersN / kPersScore;      // 256
+constexpr int kPersChunks = kPersK / 64;              // columns a lane holds
+
+struct LitPers {
+  const float* C;
+  const float* v;
+  int n, k, rounds;
+  double eps, u;
+  int32_t* selected;
+  double* step_score;
+  double* step_residual;
+  double* objpart;               // [solvers]
+  unsigned long long* col;       // [2][kPersSolvers][kPersK] column sums, epoch in the sign
+  unsigned long long* r;         // [2][kPersN] residuals, epoch in the sign
+  unsigned long long* mass;      // [2][kPersSolvers] their sums, epoch in the sign
+  double* part;                  // [blocks][n] partial scores
+  unsigned long long* flag;      // [kPersBlocks] slots: steps whose partial scores are written
+  unsigned long long* cand;      // [2][kPersBlocks] slots: score high, score low, index, each above the step
+  unsigned int* abort;
+  unsigned int poll_limit, abort_init;
+  int solvers;
+};
+
+__global__ void lit_pers_init_kernel(LitPers p, size_t words) {
+  const size_t gt = size_t(blockIdx.x) * blockDim.x + threadIdx.x, nt = size_t(gridDim.x) * blockDim.x;
+  for (size_t i = gt; i < words; i += nt) p.col[i] = 0ull;   // col, r, mass, flag and cand lie side by side
+  if (gt == 0) *p.abort = p.abort_init;
+}
+
+__device__ __forceinline__ double lane_f64(double x, int l) {
+  return __longlong_as_double((long long)lane_u64((unsigned long long)__double_as_longlong(x), l));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+  return __longlong_as_double((long long)dpp_u64<CTRL>((unsigned long long)__double_as_longlong(x)));
+}
+
+// Sums of eight values over the wave: lane l ends with the sum of value
+// (l & 7).  Halving by lane bits 0 and 1, whole rotation by 8, halving by
+// bit 2 (a rotation by 4 is one by lane ^ 4 once the values repeat every 8),
+// then the four rows of 16.
+__device__ __forceinline__ double wave_sum8(const double (&p)[8]) {
+  const int lane = threadIdx.x & 63;
+  double a[4], b[2];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const bool odd = lane & 1;
+    a[q] = (odd ? p[2 * q + 1] : p[2 * q]) + dpp_f64<0xB1>(odd ? p[2 * q] : p[2 * q + 1]);
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const bool odd = lane & 2;
+    b[q] = (odd ? a[2 * q + 1] : a[2 * q]) + dpp_f64<0x4E>(odd ? a[2 * q] : a[2 * q + 1]);
+    b[q] += dpp_f64<0x128>(b[q]);
+  }
+  const bool odd = lane & 4;
+  double x = (odd ? b[1] : b[0]) + dpp_f64<0x124>(odd ? b[0] : b[1]);
+  x += __shfl_xor(x, 16);
+  x += __shfl_xor(x, 32);
+  return x;
+}
+
+// x with the exchange's epoch in its sign; x is not negative.
+__device__ __forceinline__ unsigned long long signed_word(double x, unsigned long long epoch) {
+  return ((unsigned long long)__double_as_longlong(x) & ~kEpoch) | epoch;
+}
+__device__ __forceinline__ double word_value(unsigned long long x) { return __longlong_as_double((long long)(x & ~kEpoch)); }
+
+// The order of doubles as that of unsigned integers.
+__device__ __forceinline__ unsigned long long f64_order(double x) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  return (b & kEpoch) ? ~b : (b | kEpoch);
+}
+
+__global__ __launch_bounds__(kBlock) void lit_persistent_kernel(LitPers p) {
+  extern __shared__ float scost[];                    // [kPersScore][n] rows of the cost to score
+  const int blk = blockIdx.x, nt = gridDim.x;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __shared__ double sa[kPersK];                       // a of the round
+  __shared__ double sred[kWaves][kPersK];             // the waves' column sums; scores
+  __shared__ double shalf[kPersK];                    // sums over the second half of the blocks
+  __shared__ double sr[kPersScore];                   // residuals of the scored rows
+  __shared__ unsigned long long su[kWaves];
+  __shared__ int si[kWaves];
+  __shared__ int spick[kPersK];
+  __shared__ int sflag;
+  __shared__ double smass[kWaves];
+
+  const bool solver = blk < p.solvers;
+  // Rows of E: 8 of this wave, columns lane, lane + 64, ..; zero where there
+  // is no column yet and past n.
+  double E[8][kPersChunks];
+#pragma unroll
+  for (int q = 0; q < 8; ++q)
+#pragma unroll
+    for (int c = 0; c < kPersChunks; ++c) E[q][c] = 0.0;
+  const int jw = blk * kPersRows + w * 8;             // the wave's first row (solvers)
+  const int jl = jw + (lane & 7);                     // the lane's row
+  const double vl = solver && jl < p.n ? double(p.v[jl]) : 0.0;
+  for (int q = 0; q < kPersScore; ++q) {
+    const int j = blk * kPersScore + q;
+    for (int c = tid; c < p.n; c += kBlock) scost[q * p.n + c] = j < p.n ? p.C[size_t(j) * p.n + c] : 0.f;
+  }
+  unsigned chosen = 0;                                // of the candidates 8 blk .. 8 blk + 7
+  if (tid == 0) sflag = 0;
+  if (tid < kPersK) sa[tid] = 0.0;
+  __syncthreads();
+
+  int round = 0;                                      // exchanges of column sums so far
+  double t8 = 0.0, b8 = 1.0;                          // t and b of the lane's row
+  // Column sums of the own rows for the current b, all blocks' added up, and
+  // the new a.  False when the launch gives up.
+  auto scale_a = [&](int l) -> bool {
+    const int nc = (l + 63) >> 6;
+    double s[kPersChunks];
+#pragma unroll
+    for (int c = 0; c < kPersChunks; ++c) s[c] = 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const double bq = lane_f64(b8, q);
+#pragma unroll
+      for (int c = 0; c < kPersChunks; ++c)
+        if (c < nc) s[c] = fma(E[q][c], bq, s[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < kPersChunks; ++c)
+      if (c < nc) sred[w][c * 64 + lane] = s[c];
+    __syncthreads();
+    const unsigned long long ep = epoch_of(round);
+    unsigned long long* set = p.col + size_t(round & 1) * kPersSolvers * kPersK;
+    const int i = tid & (kPersK - 1), h = tid / kPersK;     // column, half of the blocks
+    // Every column's word every round, also of columns not in use yet: the
+    // epoch of a word tells only this round's from the one two before.
+    if (h == 0) {
+      double x = 0.0;
+      if (i < l)
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q) x += sred[q][i];
+      put(set + size_t(blk) * kPersK + i, signed_word(x, ep));
+    }
+    double sum = 0.0;
+    if (i < l) {
+      constexpr int kHalf = kPersSolvers / 2;
+      unsigned long long x[kHalf];
+#pragma unroll
+      for (int q = 0; q < kHalf; ++q) x[q] = ~ep;
+      for (unsigned int spins = 0;; ++spins) {
+        bool miss = false;
+#pragma unroll
+        for (int q = 0; q < kHalf; ++q)
+          if (h * kHalf + q < p.solvers && (x[q] & kEpoch) != ep) x[q] = get(set + size_t(h * kHalf + q) * kPersK + i);
+#pragma unroll
+        for (int q = 0; q < kHalf; ++q) miss = miss || (h * kHalf + q < p.solvers && (x[q] & kEpoch) != ep);
+        if (!miss) break;
+        if (give_up(spins, p.poll_limit, p.abort)) {
+          sflag = 1;
+          break;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < kHalf; ++q)
+        if (h * kHalf + q < p.solvers) sum += word_value(x[q]);
+    }
+    ++round;
+    if (h == 1 && i < l) shalf[i] = sum;
+    __syncthreads();
+    if (h == 0 && i < l) sa[i] = p.u / (sum + shalf[i]);
+    __syncthreads();
+    return sflag == 0;
+  };
+  // t and b of the own rows from a.
+  auto scale_b = [&](int l) {
+    const int nc = (l + 63) >> 6;
+    double x[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = 0.0;
+#pragma unroll
+    for (int c = 0; c < kPersChunks; ++c)
+      if (c < nc) {
+        const double ac = sa[c * 64 + lane];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = fma(E[q][c], ac, x[q]);
+      }
+    t8 = wave_sum8(x);
+    b8 = t8 > 0.0 ? fmin(1.0, vl / t8) : 1.0;
+  };
+  auto solve = [&](int l) -> bool {
+    b8 = 1.0;
+    for (int it = 0; it < p.rounds; ++it) {
+      if (!scale_a(l)) return false;
+      scale_b(l);
+    }
+    return true;
+  };
+
+  for (int l = 0; l < p.k; ++l) {
+    const unsigned long long ep = epoch_of(l);
+    // The residuals (step 0: the capacities) and their sum per solver.
+    if (solver) {
+      double res = vl;
+      if (l > 0) {
+        if (!solve(l)) return;
+        res = fmax(vl - b8 * t8, 0.0);
+      }
+      if (lane < 8 && jl < p.n) put(p.r + size_t(l & 1) * kPersN + jl, signed_word(res, ep));
+      double m = lane < 8 ? res : 0.0;
+      m += dpp_f64<0xB1>(m);
+      m += dpp_f64<0x4E>(m);
+      m += __shfl_xor(m, 4);
+      if (lane == 0) smass[w] = m;
+      __syncthreads();
+      if (tid == 0) {
+        double x = 0.0;
+        for (int q = 0; q < kWaves; ++q) x += smass[q];
+        put(p.mass + size_t(l & 1) * kPersSolvers + blk, signed_word(x, ep));
+      }
+    }
+    // Residuals of the rows this block scores.
+    if (tid < kPersScore) {
+      const int j = blk * kPersScore + tid;
+      double x = 0.0;
+      if (j < p.n) {
+        unsigned long long y = ~ep;
+        if (!wait_slot(p.r + size_t(l & 1) * kPersN + j, p.abort, p.poll_limit,
+                       [ep](unsigned long long z) { return (z & kEpoch) == ep; }, y))
+          sflag = 1;
+        x = word_value(y);
+      }
+      sr[tid] = x;
+    }
+    __syncthreads();
+    if (sflag) return;
+    for (int col = tid; col < p.n; col += kBlock) {
+      double x = 0.0;
+#pragma unroll
+      for (int q = 0; q < kPersScore; ++q) x = fma(sr[q], double(scost[q * p.n + col]), x);
+      put(p.part + size_t(blk) * p.n + col, x);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): this wave's stores are done
+    __syncthreads();
+    const unsigned long long tag = (unsigned long long)(l + 1);
+    if (tid == 0) put(p.flag + size_t(blk) * kSlotStride, tag);
+    // Every block's partial scores of the own candidates, added in a fixed
+    // order: thread (candidate, part) takes blocks part, part + 64, ...
+    if (tid < nt) {
+      unsigned long long y;
+      if (!wait_slot(p.flag + size_t(tid) * kSlotStride, p.abort, p.poll_limit,
+                     [tag](unsigned long long z) { return z >= tag; }, y))
+        sflag = 1;
+    }
+    __syncthreads();
+    if (sflag) return;
+    {
+      const int c = tid & (kPersScore - 1), part = tid / kPersScore;
+      const int col = min(blk * kPersScore + c, p.n - 1);
+      double x[kPersBlocks / 64];
+#pragma unroll
+      for (int q = 0; q < kPersBlocks / 64; ++q)
+        x[q] = get(p.part + size_t(min(part + 64 * q, nt - 1)) * p.n + col);
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < kPersBlocks / 64; ++q)
+        if (part + 64 * q < nt) s += x[q];
+      // Lanes 8 apart hold one candidate: the wave's eight parts, then the waves'.
+      s += dpp_f64<0x128>(s);
+      s += __shfl_xor(s, 16);
+      s += __shfl_xor(s, 32);
+      if (lane < kPersScore) sred[w][lane] = s;
+    }
+    __syncthreads();
+    if (w == 0) {
+      const int col = blk * kPersScore + lane;
+      const bool ok = lane < kPersScore && col < p.n && !((chosen >> (lane & 7)) & 1u);
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < kWaves; ++q) s += sred[q][lane & 7];
+      const unsigned long long key = ok ? ~f64_order(s) : 0ull;
+      const unsigned long long top = wave_max_u64(key);
+      const int bi = wave_min_i32(ok && key == top ? col : INT_MAX);
+      // The best one's score (none: no word of it is taken).
+      const unsigned long long bits = ~top;
+      if (lane < 3) {
+        const unsigned pay = lane == 0 ? unsigned(bits >> 32) : lane == 1 ? unsigned(bits) : unsigned(bi);
+        put(p.cand + (size_t(l & 1) * kPersBlocks + blk) * kSlotStride + lane, (tag << 32) | pay);
+      }
+    }
+    // Every block's candidate; the smallest score, then the smallest index.
+    {
+      unsigned long long key = 0ull;
+      int bi = INT_MAX;
+      if (tid < nt) {
+        const unsigned long long* slot = p.cand + (size_t(l & 1) * kPersBlocks + tid) * kSlotStride;
+        for (unsigned int spins = 0;; ++spins) {
+          const unsigned long long x0 = get(slot), x1 = get(slot + 1), x2 = get(slot + 2);
+          if ((x0 >> 32) == tag && (x1 >> 32) == tag && (x2 >> 32) == tag) {
+            bi = int(unsigned(x2));
+            key = bi == INT_MAX ? 0ull : ~((x0 << 32) | (x1 & 0xffffffffull));
+            break;
+          }
+          if (give_up(spins, p.poll_limit, p.abort)) {
+            sflag = 1;
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
+        }
+      }
+      const unsigned long long top = wave_max_u64(key);
+      const int im = wave_min_i32(key == top ? bi : INT_MAX);
+      if (lane == 0) {
+        su[w] = top;
+        si[w] = im;
+      }
+    }
+    __syncthreads();
+    if (sflag) return;
+    unsigned long long top = su[0];
+    int s = si[0];
+#pragma unroll
+    for (int q = 1; q < kWaves; ++q)
+      if (su[q] > top || (su[q] == top && si[q] < s)) {
+        top = su[q];
+        s = si[q];
+      }
+    s = min(s, p.n - 1);
+    if (s / kPersScore == blk) chosen |= 1u << (s % kPersScore);
+    if (tid == 0) {
+      spick[l] = s;
+      if (blk == 0) {
+        p.selected[l] = s;
+        if (p.step_score) {
+          const unsigned long long o = ~top;            // f64_order of the score
+          p.step_score[l] = __longlong_as_double((long long)((o & kEpoch) ? (o & ~kEpoch) : ~o));
+        }
+      }
+    }
+    if (blk == 0 && w == 1 && p.step_residual) {
+      double m = 0.0;
+      bool ok = true;
+      if (lane < p.solvers) {
+        unsigned long long y = 0;
+        ok = wait_slot(p.mass + size_t(l & 1) * kPersSolvers + lane, p.abort, p.poll_limit,
+                       [ep](unsigned long long z) { return (z & kEpoch) == ep; }, y);
+        m = word_value(y);
+      }
+      m = wave_sum(m);
+      if (lane == 0 && ok) p.step_residual[l] = m;
+    }
+    // The pick's column of E.
+    if (solver) {
+      const double x = jl < p.n ? exp(-double(p.C[size_t(jl) * p.n + s]) / p.eps) : 0.0;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const double xq = lane_f64(x, q);
+#pragma unroll
+        for (int c = 0; c < kPersChunks; ++c)
+          if (c == (l >> 6) && lane == (l & 63)) E[q][c] = xq;
+      }
+    }
+    __syncthreads();
+  }
+  if (!solver) return;
+  // The final plan and its cost.
+  if (!solve(p.k)) return;
+  double acc = 0.0;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const double bq = lane_f64(b8, q);
+    const int j = min(jw + q, p.n - 1);               // E is zero past n
+    double x = 0.0;
+#pragma unroll
+    for (int c = 0; c < kPersChunks; ++c) {
+      const int i = c * 64 + lane;
+      if (i < p.k) x = fma(sa[i] * E[q][c], double(p.C[size_t(j) * p.n + spick[i]]), x);
+    }
+    acc = fma(x, bq, acc);
+  }
+  acc = wave_sum(acc);
+  if (lane == 0) smass[w] = acc;
+  __syncthreads();
+  if (tid == 0) {
+    double x = 0.0;
+    for (int q = 0; q < kWaves; ++q) x += smass[q];
+    p.objpart[blk] = x;
+  }
+}
 
 struct LitLayout {
   size_t E, a, b, r, colpart, scorepart, objpart, chosen, total;
@@ -303,12 +711,92 @@ hipError_t solve(const LitDev& p, int l, int rounds, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// The persistent form's workspace: the words its blocks exchange, cleared
+// before each launch, then the partial scores and objective parts.
+constexpr size_t kPersWords = size_t(2) * kPersSolvers * kPersK + 2 * kPersN + 2 * kPersSolvers +
+                              size_t(kPersBlocks) * kSlotStride + size_t(2) * kPersBlocks * kSlotStride;
+bool lit_pers_serves(int64_t n, int64_t k) { return n <= kPersN && k <= kPersK; }
+size_t lit_pers_bytes(int64_t n) {
+  const size_t blocks = size_t((n + kPersScore - 1) / kPersScore);
+  return a256(kPersWords * 8) + 256 + a256(size_t(kPersSolvers) * 8) + blocks * size_t(n) * 8;
+}
+
+// Runs the persistent form if the device can hold its grid and the stream is
+// not being captured (the separate launches can be); *done says so.
+hipError_t try_persistent(const LiteralParams& q, hipStream_t stream, bool* done) {
+  *done = false;
+  if (q.follow || !lit_pers_serves(q.n, q.k) || q.workspace_bytes < lit_pers_bytes(q.n)) return hipSuccess;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return hipSuccess;
+  }
+  if (cap != hipStreamCaptureStatusNone) return hipSuccess;
+  int dev = 0, cus = 0, per_cu = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+  const void* kernel = reinterpret_cast<const void*>(lit_persistent_kernel);
+  const size_t lds = size_t(kPersScore) * q.n * sizeof(float);
+  if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, lds)) != hipSuccess) return e;
+  const int blocks = (q.n + kPersScore - 1) / kPersScore;
+  if (blocks > cus * per_cu) return hipSuccess;
+
+  char* w = static_cast<char*>(q.workspace);
+  LitPers p{};
+  p.C = q.cost;
+  p.v = q.capacity;
+  p.n = q.n;
+  p.k = q.k;
+  p.rounds = q.rounds;
+  p.eps = double(q.epsilon);
+  p.u = 1.0 / double(q.k);
+  p.selected = q.selected;
+  p.step_score = q.step_score;
+  p.step_residual = q.step_residual;
+  p.col = reinterpret_cast<unsigned long long*>(w);
+  p.r = p.col + size_t(2) * kPersSolvers * kPersK;
+  p.mass = p.r + 2 * kPersN;
+  p.flag = p.mass + 2 * kPersSolvers;
+  p.cand = p.flag + size_t(kPersBlocks) * kSlotStride;
+  w += a256(kPersWords * 8);
+  p.abort = reinterpret_cast<unsigned int*>(w);
+  w += 256;
+  p.objpart = reinterpret_cast<double*>(w);
+  w += a256(size_t(kPersSolvers) * 8);
+  p.part = reinterpret_cast<double*>(w);
+  const WaitPolicy wp = wait_policy();
+  p.poll_limit = wp.limit;
+  p.abort_init = wp.preset;
+  p.solvers = (q.n + kPersRows - 1) / kPersRows;
+  lit_pers_init_kernel<<<32, 256, 0, stream>>>(p, kPersWords);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  void* args[] = {&p};
+  if ((e = hipLaunchCooperativeKernel(kernel, dim3(blocks), dim3(kBlock), args, lds, stream)) != hipSuccess) return e;
+  if ((e = launch_mark_aborted(p.abort, p.selected, p.k, stream)) != hipSuccess) return e;
+  if (q.objective) {
+    LitDev d{};
+    d.nrb = p.solvers;
+    d.objpart = p.objpart;
+    d.objective = q.objective;
+    lit_objective_sum_kernel<<<1, 64, 0, stream>>>(d);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  *done = true;
+  return hipSuccess;
+}
+
 }  // namespace
 
-size_t sgs_literal_workspace_bytes(int64_t n, int64_t k) { return lit_layout(n, k).total; }
+size_t sgs_literal_workspace_bytes(int64_t n, int64_t k) {
+  return std::max(lit_layout(n, k).total, lit_pers_serves(n, k) ? lit_pers_bytes(n) : size_t(0));
+}
 
 hipError_t launch_sgs_literal(const LiteralParams& q, hipStream_t stream) {
   if (q.n < 1 || q.k < 1 || q.k > q.n || q.k > kLitMaxK || q.rounds < 1) return hipErrorInvalidValue;
+  bool done = false;
+  const hipError_t pe = try_persistent(q, stream, &done);
+  if (pe != hipSuccess || done) return pe;
   const LitLayout L = lit_layout(q.n, q.k);
   char* w = static_cast<char*>(q.workspace);
   LitDev p;

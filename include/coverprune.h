@@ -85,7 +85,7 @@ typedef struct {
 } cp_fst_weights;
 
 /* SGS flags (the same greedy either way; see coverprune_sgs_select). */
-#define CP_SGS_DENSE 0u       /* every step re-evaluates every candidate's gain over the whole cost matrix */
+#define CP_SGS_DENSE 0u       /* gains over the whole cost matrix, for any data; fast where the data allow it */
 #define CP_SGS_INCREMENTAL 1u /* gains computed once, then updated from the rows whose best cost drops */
 #define CP_SGS_COMPACT 2u     /* with CP_SGS_INCREMENTAL: the schedule with the small workspace */
 
@@ -176,7 +176,13 @@ cp_status coverprune_fst_capacity(const void* feats, cp_dtype dtype, int64_t n, 
  *   c0        cost of leaving a target uncovered; coverprune_uncovered_cost(w)
  *             (the largest value C can take) is the usual choice
  *   flags     CP_SGS_DENSE: every step sums every candidate's gain over the
- *             whole matrix (K full reads of the cost).
+ *             whole matrix (K full reads of the cost), in float64.  Up to
+ *             n = 8192, with the workspace of coverprune_sgs_workspace, the
+ *             picks come from the incremental form instead when a check on
+ *             the device finds every cost >= 0 and every capacity finite,
+ *             >= 0 and, if positive, of at least 36 bits on that form's grid;
+ *             otherwise, or with a workspace for the sweeps alone, the whole
+ *             matrix is read each step.
  *             CP_SGS_INCREMENTAL: the gains are summed once at b = c0 and then
  *             updated, step by step, from the rows of the targets whose best
  *             cost the pick lowers (their old and new b); the terms are the
@@ -216,7 +222,8 @@ cp_status coverprune_fst_capacity(const void* feats, cp_dtype dtype, int64_t n, 
  */
 /* Workspace for one form (flags as for coverprune_sgs_select; 0 for flags it
  * does not accept): the dense form needs about 9 MB at n = 16384 (private
- * best costs and float64 partial gains of up to 64 row panels), the
+ * best costs and float64 partial gains of up to 64 row panels), plus the
+ * incremental form's workspace up to n = 8192 (it runs without it), the
  * incremental form 4 n + 45 bytes per token up to n = 32768 (plus up to
  * 2 KB per token for the early steps' sums when n <= 16384, and 4 KB per
  * token for the candidate lists when n <= 16384 and k > 128) and about 45

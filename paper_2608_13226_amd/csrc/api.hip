@@ -165,7 +165,10 @@ cp_status coverprune_sgs_select(const float* cost, int64_t n, const float* capac
     return fail(CP_ERR_UNSUPPORTED, "unknown flags 0x%x", flags);
   if (!cost || !capacity || !selected) return fail(CP_ERR_INVALID_ARG, "cost, capacity and selected must be non-NULL");
   if (!aligned16(cost)) return fail(CP_ERR_INVALID_ARG, "cost is not 16-byte aligned");
-  cp_status st = check_workspace(workspace, workspace_bytes, coverprune_sgs_workspace(n, k, flags));
+  // The dense form also runs in the workspace of its sweeps alone.
+  cp_status st = check_workspace(workspace, workspace_bytes,
+                                 flags == CP_SGS_DENSE ? cp::sgs_sweep_workspace_bytes(n, k)
+                                                       : coverprune_sgs_workspace(n, k, flags));
   if (st != CP_OK) return st;
 
   cp::SgsParams p;

@@ -31,6 +31,17 @@
 // Across strips the packed key compares gains truncated to 44 bits (relative
 // resolution 2^-32) and breaks ties by the smaller index; within a strip the
 // comparison is exact.
+//
+// The sweeps read the whole cost every step, though a pick changes the terms
+// of few targets after the first steps.  Up to kFastN tokens the call
+// therefore runs the incremental greedy (the rows schedule of k_sgs_inc.hip):
+// the same float32 differences and exact products, summed in 64-bit fixed
+// point on a grid of 2^-62 of the total instead of in float64, so gains differ
+// by far less than the differences' own rounding (2^-24).  It serves costs in
+// [0, inf] and capacities in [0, inf) whose smallest positive one is not below
+// 2^-26 of the grid's range (kUnfitBits); its first pass checks that, and
+// the sweeps run only when it raised `unfit`.  n = 4096, K = 410: 10.8 ms of
+// sweeps (26 us a step, 2.6 TB/s from the Infinity Cache).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -70,6 +81,7 @@ struct SgsDev {
   unsigned int* abort;       // set when the step wait gives up
   unsigned int poll_limit;   // polls before it gives up (WaitPolicy)
   unsigned int abort_init;   // the abort flag's value at launch
+  const unsigned int* gate;  // the launch runs only when this word is set (null: always)
   int P, S, rows;            // panels, strips, rows per panel
 };
 
@@ -144,6 +156,10 @@ __device__ double block_sum(double x, double* sd) {
 
 __global__ void sgs_init_kernel(SgsDev a) {
   const int gt = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+  if (a.gate && !*a.gate) {
+    if (gt == 0) *a.abort = 0u;
+    return;
+  }
   for (int j = gt; j < a.n; j += nt) {
     a.mask[j] = 0u;
     if (a.assign) a.assign[j] = -1;
@@ -291,6 +307,7 @@ __global__ __launch_bounds__(BT) void sgs_dense_kernel(SgsDev a) {
   __shared__ unsigned int s_prev;
   __shared__ int s_t;
 
+  if (a.gate && !*a.gate) return;
   const int items = a.P * a.S;
   int tprev = -1;
   for (int step = 0; step < a.k; ++step) {
@@ -401,9 +418,25 @@ hipError_t max_coresident(int& blocks) {
 
 }  // namespace
 
-size_t sgs_workspace_bytes(int64_t n, int64_t k) { return layout(n, k).total; }
+// Beyond it the incremental form's copy of the cost would take the workspace
+// from megabytes past 256 MB; the sweeps' is 2 MB at n = 4096, 9 MB at 16384.
+constexpr int kFastN = 8192;
+
+size_t sgs_sweep_workspace_bytes(int64_t n, int64_t k) { return layout(n, k).total; }
+
+size_t sgs_workspace_bytes(int64_t n, int64_t k) {
+  return layout(n, k).total + (n <= kFastN ? sgs_inc_workspace_bytes(n, k, false) : 0);
+}
 
 hipError_t launch_sgs_dense(const SgsParams& p, hipStream_t stream) {
+  const unsigned int* gate = nullptr;
+  if (p.n <= kFastN && p.c0 > 0.f && p.workspace_bytes >= sgs_workspace_bytes(p.n, p.k)) {
+    SgsParams q = p;
+    q.workspace = static_cast<char*>(p.workspace) + layout(p.n, p.k).total;
+    q.workspace_bytes = p.workspace_bytes - layout(p.n, p.k).total;
+    const hipError_t e = launch_sgs_checked(q, &gate, stream);
+    if (e != hipSuccess) return e;
+  }
   const bool vec4 = (p.n % 4) == 0;
   int max_blocks = 0;
   hipError_t e = vec4 ? max_coresident<true>(max_blocks) : max_coresident<false>(max_blocks);
@@ -441,6 +474,7 @@ hipError_t launch_sgs_dense(const SgsParams& p, hipStream_t stream) {
   const WaitPolicy wp = wait_policy();
   a.poll_limit = wp.limit;
   a.abort_init = wp.preset;
+  a.gate = gate;
   a.P = P;
   a.S = S;
   a.rows = rows;

@@ -52,6 +52,7 @@ constexpr int kChunk = 16;         // of which the rows read together
 
 // The greedy of one scene as run by block `blk` of the scene's `nb` blocks.
 __device__ __forceinline__ void inc_body(const IncDev& a, int blk, int nb) {
+  if (unfit(a)) return;
   extern __shared__ unsigned long long smem[];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int lo = blk * a.W;
@@ -475,6 +476,7 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
   __shared__ unsigned long long sk1[kSpec ? kMaxBlocks : 1], sk2[kSpec ? kMaxBlocks : 1];
   __shared__ long long sdr[kWaves];
 
+  if (unfit(a)) return;
   // After the early kernel the first step is the one it stopped before.
   if (a.start && *a.abort) return;
   const int k_begin = a.start ? int(*a.start) : a.k_begin;
@@ -887,11 +889,16 @@ constexpr int kEarlyShare = 128;                      // hits a block takes per 
 constexpr int kEarlyMinHits = 512;                    // steps with fewer hits go back to the rows kernel
 
 int early_ldp(int64_t n) { return int((n + 1 + 63) / 64 * 64); }
-bool early_for(int64_t n, int W) { return n <= kEarlyMaxN && W <= kRowsMaxW; }
+// Up to kEarlyMinN tokens the rows kernel serves the first steps as well, in
+// one launch less (the prune of 1024 tokens, K = 102: 0.54 ms with the early
+// kernel's steps of 24 us, 0.39 without; 2048 tokens, K = 409: 0.97 and 0.94).
+constexpr int kEarlyMinN = 2048;
+bool early_for(int64_t n, int W) { return n > kEarlyMinN && n <= kEarlyMaxN && W <= kRowsMaxW; }
 
 // NG 64-column groups per block, as in the rows kernel that continues.
 template <int NG>
 __device__ __forceinline__ void early_body(const IncDev& a, int blk, int nb) {
+  if (!a.epart) return;                               // a scene of a batch without early steps
   extern __shared__ unsigned long long smem[];
   constexpr int RL = 8;                               // chunk loads per wave: n <= kRowChunk kWaves RL
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -910,6 +917,7 @@ __device__ __forceinline__ void early_body(const IncDev& a, int blk, int nb) {
   __shared__ float sbo[kEarlyShare], sbn[kEarlyShare];
   __shared__ double svs[kEarlyShare];                 // and its capacity scaled for fx_diff
 
+  if (unfit(a)) return;
   const int S = *a.scale;
   for (int j = tid; j < a.ldt; j += kBlock) sball[j] = j < a.n ? a.c0 : -__builtin_inff();
   for (int i = tid; i < cnt; i += kBlock) ssel[i] = 0;
@@ -1228,7 +1236,7 @@ int list_ent(int64_t n, int W) { return int(std::min<size_t>(65535, (size_t(kLis
 // lie at the start of the row itself).
 __global__ __launch_bounds__(256) void list_build_kernel(IncDev a) {
   __shared__ uint2 sl[4][kListCap];
-  if (*a.abort) return;
+  if (*a.abort || unfit(a)) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int c = blockIdx.x * 4 + w;
   if (c >= a.n) return;
@@ -1338,7 +1346,7 @@ __device__ __forceinline__ void publish_list(const unsigned long long* sG, const
 // scene's `nb` blocks (NG columns per lane: W <= 64 NG).
 template <int NG>
 __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
-  if (*a.abort || a.k_begin >= a.k) return;
+  if (*a.abort || a.k_begin >= a.k || unfit(a)) return;
   extern __shared__ unsigned long long smem[];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lo = blk * a.W;
@@ -1917,12 +1925,27 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
 template <int NG>
 __global__ __launch_bounds__(kListBlock) void sgs_list_kernel(IncDev a) { list_body<NG>(a, blockIdx.x, gridDim.x); }
 
+// The dense form's guard (k_sgs.hip): a term below its target's largest one
+// by 2^-12 still has the 24 bits of the float32 difference in it.
+constexpr int kUnfitBits = 36;
+
 // The fixed-point scale of a scene (one block; the sum in the same order as
 // every block of the greedy would take it).
 __global__ __launch_bounds__(kBlock) void inc_scale_kernel(IncDev a, int* scale) {
   __shared__ double sd[kWaves];
   const int S = fixed_scale(a, sd);
   if (threadIdx.x == 0) *scale = S;
+  if (a.abort_init & 2u) {
+    // Capacities the fixed point does not hold: negative, infinite, NaN, or a
+    // positive one whose largest term keeps fewer than kUnfitBits bits.
+    bool bad = false;
+    for (int j = threadIdx.x; j < a.n; j += kBlock) {
+      const float v = a.v[j];
+      bad = bad || !(v >= 0.f && v < __builtin_inff()) ||
+            (v > 0.f && __builtin_ldexp(double(v) * double(a.c0), S) < double(1ull << kUnfitBits));
+    }
+    if (bad) atomicOr(a.abort + kUnfitWord, 1u);
+  }
 }
 
 // Step-0 gains, every row at b = c0, split over a grid of (column strip,
@@ -1946,7 +1969,7 @@ __host__ __device__ __forceinline__ int pass_rows(int n, int P) {
   return ((n + P - 1) / P + kPassRows - 1) / kPassRows * kPassRows;
 }
 
-template <bool WT>
+template <bool WT, bool CHECK>
 __global__ __launch_bounds__(kPassThreads) void inc_first_pass_kernel(IncDev a, long long* part) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int lo = blockIdx.x * a.W, cnt = max(0, min(a.n, lo + a.W) - lo);
@@ -1960,6 +1983,7 @@ __global__ __launch_bounds__(kPassThreads) void inc_first_pass_kernel(IncDev a, 
     // The next round's loads are issued before the current round's terms
     // are formed; two accumulators.
     long long g0 = 0, g1 = 0;
+    bool bad = false;
     float xn[kPassRows], vn[kPassRows];
     auto load = [&](int j0) {
 #pragma unroll
@@ -1977,6 +2001,7 @@ __global__ __launch_bounds__(kPassThreads) void inc_first_pass_kernel(IncDev a, 
       for (int u = 0; u < kPassRows; ++u) {
         x[u] = xn[u];
         vj[u] = vn[u];
+        if (CHECK) bad = bad || !(x[u] >= 0.f);
       }
       if (jr + kPassTile < r1) load(j0 + kPassTile);   // rows past r1 load as zero terms
 #pragma unroll
@@ -2002,6 +2027,7 @@ __global__ __launch_bounds__(kPassThreads) void inc_first_pass_kernel(IncDev a, 
         __syncthreads();
       }
     }
+    if (CHECK && __ballot(bad) && lane == 0) atomicOr(a.abort + kUnfitWord, 1u);
     red[tid] = g0 + g1;
     __syncthreads();
     if (tid < 64 && cc + tid < cnt) {
@@ -2018,6 +2044,7 @@ __global__ __launch_bounds__(kPassThreads) void inc_first_pass_kernel(IncDev a, 
 // with its own slots, change lists and abort flag, so the scenes' greedies
 // proceed independently side by side.
 constexpr int kMaxBatch = 16;
+constexpr int kBatchListK = 32;                       // batches of no more picks do without the list kernel
 
 struct IncBatch {
   int count;
@@ -2058,14 +2085,21 @@ __global__ __launch_bounds__(kListBlock) void sgs_list_batch_kernel(IncBatch b) 
 // at most two columns per lane; otherwise the exchange form.
 bool use_rows(int64_t n, int W) { return n <= kRowsMaxN && W <= kRowsMaxW; }
 
+// A short greedy (few picks of a small scene) takes the exchange form's single
+// launch whatever the schedule asked for: the rows form spends some 0.1 ms on
+// its launches and first steps before its steps get cheaper than the exchange
+// form's 5 to 7 us (k = 12 of 256 tokens: 115 against 160 us, 30 of 300: 210
+// against 185, 51 of 1024: 390 against 292).  Same result.
 // Blocks of a scene's greedy, and whether it is the rows form.  The rows form
 // takes one block per kRowsPer tokens (up to one per compute unit: the early
 // steps and the hits' row segments spread over more of the chip, 4096 tokens
 // 0.05 ms faster than with one per 32), the exchange form one per 64.
 constexpr int kRowsPer = 16;
-int inc_blocks(int64_t n, int cus, bool compact, bool* rows) {
+constexpr int kShortN = 2048, kShortK = 20;
+bool short_greedy(int64_t n, int64_t k) { return n <= kShortN && k <= kShortK; }
+int inc_blocks(int64_t n, int64_t k, int cus, bool compact, bool* rows) {
   const int nb = blocks_for(n, cus, kRowsPer);
-  *rows = !compact && use_rows(n, int((n + nb - 1) / nb));
+  *rows = !compact && !short_greedy(n, k) && use_rows(n, int((n + nb - 1) / nb));
   return *rows ? nb : blocks_for(n, cus, 64);
 }
 
@@ -2157,11 +2191,13 @@ IncDev inc_dev(const SgsParams& p, char* w, int nb, int W, bool rows) {
   a.scale = reinterpret_cast<const int*>(w + M.scale);
   a.k_begin = 0;
   a.k_end = p.k;
-  if (rows && early_for(p.n, W)) {
+  if (rows && p.n <= kEarlyMaxN) {
     a.ho_gain = reinterpret_cast<long long*>(w + M.ho_gain);
     a.ho_sel = reinterpret_cast<unsigned char*>(w + M.ho_sel);
     a.ho_b = reinterpret_cast<float*>(w + M.ho_b);
     a.ho_misc = reinterpret_cast<long long*>(w + M.misc);
+  }
+  if (rows && early_for(p.n, W)) {
     a.epart = reinterpret_cast<long long*>(w + M.epart);
     a.ldp = early_ldp(p.n);
     a.eshares = int(std::min<size_t>(nb, M.epart_bytes / (size_t(a.ldp) * 8)));
@@ -2186,10 +2222,14 @@ hipError_t launch_first_pass(const IncDev& a, int nb, hipStream_t stream) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   long long* part = const_cast<long long*>(a.part);
-  if (a.T)
-    inc_first_pass_kernel<true><<<dim3(nb, a.P), kPassThreads, 0, stream>>>(a, part);
+  if (a.T && (a.abort_init & 2u))
+    inc_first_pass_kernel<true, true><<<dim3(nb, a.P), kPassThreads, 0, stream>>>(a, part);
+  else if (a.abort_init & 2u)
+    inc_first_pass_kernel<false, true><<<dim3(nb, a.P), kPassThreads, 0, stream>>>(a, part);
+  else if (a.T)
+    inc_first_pass_kernel<true, false><<<dim3(nb, a.P), kPassThreads, 0, stream>>>(a, part);
   else
-    inc_first_pass_kernel<false><<<dim3(nb, a.P), kPassThreads, 0, stream>>>(a, part);
+    inc_first_pass_kernel<false, false><<<dim3(nb, a.P), kPassThreads, 0, stream>>>(a, part);
   return hipGetLastError();
 }
 
@@ -2221,14 +2261,14 @@ const void* list_kernel(int W) {
 // The greedy's launches; with `fused` the step-0 gains and T were written by
 // fst_epilogue_sgs_kernel (and the scale before it), so the first pass is
 // skipped and the gains come from its partial sums.
-hipError_t run_incremental(const SgsParams& p, bool compact, const SgsFused* fused, hipStream_t stream) {
+hipError_t run_incremental(const SgsParams& p, bool compact, const SgsFused* fused, hipStream_t stream,
+                           const unsigned int** unfit = nullptr) {
   int cus = 0;
   hipError_t e = hipError_t(device_cus(&cus));
   if (e != hipSuccess) return e;
   bool rows = false;
-  const int nb = inc_blocks(p.n, cus, compact, &rows);
+  const int nb = inc_blocks(p.n, p.k, cus, compact, &rows);
   const int W = (p.n + nb - 1) / nb;
-  if (fused && !rows) return hipErrorInvalidValue;
   const void* kernel = rows ? rows_kernel(p.n, W) : reinterpret_cast<const void*>(sgs_inc_kernel);
   const size_t lds = rows ? lds_rows(W, p.n) : lds_for(W);
   if ((e = fits(kernel, lds)) != hipSuccess) return e;
@@ -2237,6 +2277,10 @@ hipError_t run_incremental(const SgsParams& p, bool compact, const SgsFused* fus
   if (fused) {
     a.part = fused->part;
     a.P = fused->P;
+  }
+  if (unfit) {
+    a.abort_init |= 2u;
+    *unfit = a.abort + kUnfitWord;
   }
   // The early kernel runs the first steps, while they improve many targets,
   // the rows kernel those up to the list phase (or the end), the list kernel
@@ -2273,14 +2317,17 @@ hipError_t launch_sgs_incremental(const SgsParams& p, bool compact, hipStream_t 
   return run_incremental(p, compact, nullptr, stream);
 }
 
+hipError_t launch_sgs_checked(const SgsParams& p, const unsigned int** unfit, hipStream_t stream) {
+  return run_incremental(p, false, nullptr, stream, unfit);
+}
+
 // coverprune_prune: the rows schedule's workspace, then the epilogue's
 // partial gains, [n / 64][n] 64-bit integers.
 bool sgs_fused_fits(int64_t n) {
   int cus = 0;
   if (device_cus(&cus) != hipSuccess || n < 64 || n % 64 != 0) return false;
-  bool rows = false;
-  inc_blocks(n, cus, false, &rows);
-  return rows;
+  const int nb = blocks_for(n, cus, kRowsPer);
+  return use_rows(n, int((n + nb - 1) / nb));
 }
 
 size_t sgs_fused_workspace_bytes(int64_t n, int64_t k) {
@@ -2291,8 +2338,7 @@ hipError_t sgs_fused_prepare(const SgsParams& p, SgsFused* f, hipStream_t stream
   int cus = 0;
   hipError_t e = hipError_t(device_cus(&cus));
   if (e != hipSuccess) return e;
-  bool rows = false;
-  const int nb = inc_blocks(p.n, cus, false, &rows);
+  const int nb = blocks_for(p.n, cus, kRowsPer);
   IncDev a = inc_dev(p, static_cast<char*>(p.workspace), nb, (p.n + nb - 1) / nb, true);
   f->T = a.T;
   f->ldt = a.ldt;
@@ -2324,11 +2370,13 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
   // One block per compute unit in all: every scene starts with one, then the
   // scene with the most tokens per block gains one (up to its own cap of one
   // block per 64 tokens, at most kMaxBlocks) until the units run out.
+  bool rows = false;
+  for (int s = 0; s < count; ++s) rows = rows || (!compact && !short_greedy(p[s].n, p[s].k));
   int nb[kMaxBatch], cap[kMaxBatch];
   int used = count;
   for (int s = 0; s < count; ++s) {
     nb[s] = 1;
-    cap[s] = blocks_for(p[s].n, cus, compact ? 64 : kRowsPer);
+    cap[s] = blocks_for(p[s].n, cus, rows ? kRowsPer : 64);
   }
   while (used < cus) {
     int best = -1;
@@ -2345,20 +2393,23 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
     ++nb[best];
     ++used;
   }
-  // The rows form when every scene allows it (one form per launch), with the
-  // early and the list kernel when they serve every scene.
-  bool rows = !compact, early = !compact, lists = false;
+  // The rows form when every scene allows it (one form per launch) and one is
+  // not short, with the early and list kernels for the scenes they serve.
+  // A handful of picks does not pay for two more launches (three scenes of 256
+  // tokens, K = 25: 221 us with the list kernel).
+  bool early = false, lists = false;
+  for (int s = 0; s < count; ++s) lists = lists || (rows && p[s].k > kBatchListK);
   int wmax = 0, nmax = 0;
   for (int s = 0; s < count; ++s) {
     const int W = (p[s].n + nb[s] - 1) / nb[s];
     rows = rows && use_rows(p[s].n, W);
-    early = early && early_for(p[s].n, W);
-    lists = lists || lists_for(p[s].n, p[s].k, W);
+    early = early || early_for(p[s].n, W);
+    lists = lists && p[s].n <= kListMaxN && W <= kRowsMaxW;
     wmax = std::max(wmax, W);
     nmax = std::max(nmax, p[s].n);
   }
-  early = early && rows;
-  lists = lists && early;
+  lists = lists && rows;
+  early = early && lists;
   IncBatch b{};
   b.count = count;
   b.g0[0] = 0;
@@ -2368,7 +2419,7 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
     const int W = (p[s].n + nb[s] - 1) / nb[s];
     IncDev& a = b.scene[s];
     a = inc_dev(p[s], w + off, nb[s], W, rows);
-    if (!early) {
+    if (!lists) {
       a.epart = nullptr;
       a.lists = nullptr;
       a.k_end = a.k;
@@ -2394,10 +2445,13 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
   void* args[] = {&b};
   if (early) {
     if ((e = hipLaunchCooperativeKernel(ekernel, dim3(used), dim3(kBlock), args, lds, stream)) != hipSuccess) return e;
-    for (int s = 0; s < count; ++s) b.scene[s].start = b.scene[s].ho_misc + 2;
+    for (int s = 0; s < count; ++s)
+      if (b.scene[s].epart) b.scene[s].start = b.scene[s].ho_misc + 2;
   }
   if ((e = hipLaunchCooperativeKernel(kernel, dim3(used), dim3(kBlock), args, lds, stream)) != hipSuccess) return e;
-  if (lists) {
+  bool any = false;
+  for (int s = 0; s < count; ++s) any = any || b.scene[s].lists;
+  if (any) {
     for (int s = 0; s < count; ++s) {
       IncDev& a = b.scene[s];
       a.k_begin = a.k_end;

@@ -62,13 +62,21 @@ struct SgsParams {
   size_t workspace_bytes;
 };
 
+// Dense form.  Up to n = 8192 it asks for the workspace of the incremental
+// form too and runs that instead of the sweeps when the data allow it (see
+// k_sgs.hip); sgs_sweep_workspace_bytes is what the sweeps alone need.
 size_t sgs_workspace_bytes(int64_t n, int64_t k);
+size_t sgs_sweep_workspace_bytes(int64_t n, int64_t k);
 hipError_t launch_sgs_dense(const SgsParams& p, hipStream_t stream);
 // Incremental form: the rows schedule (workspace about 4 n bytes per token)
 // unless `compact` or the scene is too large for it, else the exchange
 // schedule (about 16 bytes per token).
 size_t sgs_inc_workspace_bytes(int64_t n, int64_t k, bool compact);
 hipError_t launch_sgs_incremental(const SgsParams& p, bool compact, hipStream_t stream);
+// The rows schedule with its data checked on the device: *unfit (a word of
+// the workspace) is set when they are outside the fixed point's domain, and
+// the outputs are then to be computed by another launch.
+hipError_t launch_sgs_checked(const SgsParams& p, const unsigned int** unfit, hipStream_t stream);
 // The incremental greedy after launch_fst_epilogue_sgs (coverprune_prune):
 // the rows schedule, whose T and step-0 partial gains that epilogue writes.
 // sgs_fused_fits: n a multiple of 64 that the rows schedule serves on this

@@ -58,7 +58,7 @@ struct IncDev {
   unsigned long long* cand;   // [2][blocks] packed candidate | epoch << 63
   unsigned int* abort;        // set when a wait gives up
   unsigned int poll_limit;    // polls before a wait gives up (WaitPolicy)
-  unsigned int abort_init;    // the abort flag's value at launch (WaitPolicy)
+  unsigned int abort_init;    // bit 0: the abort flag's value at launch (WaitPolicy); bit 1: check the data
   int W;                      // rows and columns per block
   unsigned int w_magic;       // floor(2^32 / W) + 1: block_of(c) = c / W by one high multiply
   float* T;                   // rows form only: [n][ldt] source-major copy, T[s][t] = C(s, t)
@@ -85,6 +85,12 @@ struct IncDev {
   int ldp, eshares;
   const long long* start;
 };
+
+// With the data checked, word kUnfitWord after the abort flag is set when they
+// are outside the fixed point's domain, and the launches after the first pass
+// leave at once.
+constexpr int kUnfitWord = 16;
+__device__ __forceinline__ bool unfit(const IncDev& a) { return (a.abort_init & 2u) && a.abort[kUnfitWord]; }
 
 // The block that owns column c: c / W as the high word of c times
 // floor(2^32 / W) + 1, exact for c < 2^18 and 2 <= W <= 2^13 (the product
@@ -166,7 +172,8 @@ __global__ void sgs_inc_init_kernel(IncDev a) {
   }
   for (int j = gt; j < a.n; j += nt)
     if (a.assign) a.assign[j] = -1;
-  if (gt == 0) *a.abort = a.abort_init;
+  if (gt == 0) *a.abort = a.abort_init & 1u;
+  if (gt == 0) a.abort[kUnfitWord] = 0u;
 }
 
 // Wave reductions without LDS traffic: DPP moves within each row of 16

@@ -148,7 +148,7 @@ cp_status coverprune_fst_cost(const void* feats, cp_dtype dtype, int64_t n, int6
  *   alpha     term weights, finite and >= 0 (the experiments use 1, Sec. 5.1)
  *   capacity  [n] float output v, the input of the greedy and of Lite
  *   score     [n] double output r (may be NULL)
- *   workspace about (4 + 24 n_nb) bytes per token
+ *   workspace about (20 + 28 n_nb) bytes per token
  */
 typedef struct {
   float alpha_f, alpha_x, alpha_tau;

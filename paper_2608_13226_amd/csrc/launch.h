@@ -113,6 +113,12 @@ hipError_t launch_step_floor(const float* rows, int n_rows, int row_len, int rou
 
 // Nearest-neighbour tables: out [n, g], n <= 32768, g <= min(n, 1024).
 hipError_t launch_knn(const float* pos, int n, int g, int32_t* out, hipStream_t stream);
+// The same tables with scratch space: the tokens in spatial order, whose chunks'
+// bounding boxes rule most of them out.  spos [n] (x, y, z, token as bits) is
+// left for the caller's use; boxes holds knn_boxes_bytes(n).
+size_t knn_boxes_bytes(int64_t n);
+hipError_t launch_knn_sorted(const float* pos, int n, int g, int32_t* out, float4* spos, void* boxes,
+                             hipStream_t stream);
 
 // The greedy step solved as written: entropic semi-relaxed transport per step.
 struct LiteralParams {

@@ -377,7 +377,7 @@ def main():
     # steps are not counted.  The unit is the whole sgs_select call (its
     # kernels run back to back on one stream: slot clearing, scale, first
     # pass, the early kernel while steps lower many targets, the rows kernel
-    # to step 128, list build, list kernel), so one pair of events brackets
+    # to step n / 128, list build, list kernel), so one pair of events brackets
     # it; inside coverprune_prune the same kernels run without the first
     # pass.  The compact schedule (changes exchanged
     # between blocks, no copy) is timed beside it.
@@ -432,7 +432,7 @@ def main():
         "greedy_over_floor": round(s_ms * 1e3 / k / step_floor_us, 3), "rounds": floor_rounds,
         "note": "coverprune_step_floor: rounds of the greedy's candidate exchange (+ the dependent read of the "
                 "winner's 64 KB row); greedy_us_per_step is the whole sgs_select call over K, whose steps "
-                "after the 128th skip the exchange when the winner is predicted"}
+                "after the first n / 128 share an exchange among a dozen or more"}
 
     # Local greedy (Eq. 13) on the same cost: the g-nearest tables, then the
     # greedy with gains over each candidate's table row.  The paper leaves g

@@ -351,15 +351,6 @@ __device__ __forceinline__ int fixed_scale(const IncDev& a, double* sd) {
 // on r's gain after the step; if its truncated gain is strictly above U, r is
 // the next winner (whatever the indices), every block knows it, and the next
 // step runs without an exchange, on r's row of T loaded during this step.
-__device__ __forceinline__ void publish_rows(const long long* sG, const unsigned char* ssel, int lo, int cnt, int S,
-                                             unsigned long long* slot, unsigned long long epoch) {
-  if (threadIdx.x >= 64) return;
-  const unsigned long long mine = column_key(sG, ssel, lo, threadIdx.x, cnt, S);
-  const unsigned long long k1 = wave_max_u64(mine);
-  const unsigned long long k2 = wave_max_u64(mine == k1 ? kNoCandidate : mine);
-  if (threadIdx.x < 2) put(slot + threadIdx.x, (threadIdx.x ? k2 : k1) | epoch);
-}
-
 // A lower bound on the fixed-point gain g behind a key: the key keeps the
 // top bits of the float64 value of g 2^-S (rounded to nearest from 64 bits,
 // then truncated), so scaling it back can exceed g by at most half a unit in
@@ -368,46 +359,6 @@ __device__ __forceinline__ long long key_gain_floor(unsigned long long key, int 
   const double d = __longlong_as_double((long long)((key >> kIndexBits) << (kIndexBits + 1)));
   const long long G = (long long)__builtin_ldexp(d, S);
   return max(0ll, G - (G >> 52) - 1);
-}
-
-// read_winner for two-word slots: thread i < nb polls both words of block
-// i's slot and stores them (epoch bits cleared) in sk1 and sk2.  Returns the
-// winner's index, -1 when the launch is aborting.
-__device__ int read_winner_rows(const unsigned long long* slots, unsigned long long epoch, int nb, unsigned int* abort,
-                                unsigned int limit, unsigned long long* su, int* sflag, unsigned long long* sk1,
-                                unsigned long long* sk2) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  unsigned long long best = 0ull;
-  if (tid == 0) *sflag = 0;
-  __syncthreads();
-  if (tid < nb) {
-    const unsigned long long* p = slots + size_t(tid) * kSlotStride;
-    bool done = false;
-    for (unsigned int spins = 0; !done; ++spins) {
-      const unsigned long long x0 = get(p), x1 = get(p + 1);
-      if ((x0 & kEpoch) == epoch && (x1 & kEpoch) == epoch) {
-        best = x0 & ~kEpoch;
-        sk1[tid] = best;
-        sk2[tid] = x1 & ~kEpoch;
-        done = true;
-      } else {
-        if (give_up(spins, limit, abort)) {
-          *sflag = 1;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-    }
-  }
-  best = wave_max_u64(best);
-  if (lane == 0) su[w] = best;
-  __syncthreads();
-  unsigned long long m = su[0];
-#pragma unroll
-  for (int q = 1; q < kWaves; ++q) m = su[q] > m ? su[q] : m;
-  const bool aborting = *sflag != 0;
-  __syncthreads();
-  return aborting ? -1 : int(kIndexMask - (m & kIndexMask));
 }
 
 constexpr int kTrackMax = 256;   // hits of a step that still tracks the runner-up
@@ -513,8 +464,8 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
     if (tid < kWaves) sLw[tid] = tid == 0 ? L0 : 0;
   }
 
-  // Slot sets and epochs count exchanges, which predicted steps skip.  A
-  // continuing launch finds its first exchange's candidates published.
+  // Slot sets and epochs count exchanges, which predicted steps skip.  After
+  // the early kernel the first exchange's candidates are published.
   int xc = resume ? int(a.ho_misc[1]) : 0;
   if (!resume) {
     if (kSpec)
@@ -832,8 +783,8 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
     for (int q = 0; q < kWaves; ++q) L += sLw[q];
     a.step_obj[obj_step] = fx_to_double(L, S);
   }
-  // Hand the state over to the launch that continues (the last step
-  // published the candidates of the next exchange).
+  // Hand the state over to the list phase, which starts with an exchange of
+  // its own.
   if (a.k_end < a.k) {
     for (int i = tid; i < cnt; i += kBlock) {
       a.ho_gain[lo + i] = sG[i];
@@ -879,8 +830,8 @@ __global__ __launch_bounds__(kBlock) void sgs_rows_kernel(IncDev a) { rows_body<
 // The kernel runs while a step improves at least kEarlyMinHits targets, and
 // at most until the lists take over (or to the end), then hands its state
 // to the rows kernel as the rows kernel hands it to the list kernel, with the
-// next step in ho_misc[2].  One column group only (n <= kEarlyMaxN): a
-// thread holds the changes of n / kBlock columns.
+// next step in ho_misc[2].  A thread holds the changes of n / kBlock columns
+// (n <= kEarlyMaxN).
 constexpr int kEarlyMaxN = kRowChunk * kWaves * 8;    // 16384, the one-group rows kernel's reach
 constexpr int kEarlyCols = kEarlyMaxN / kBlock;       // columns per thread: 32
 constexpr int kEarlyPass = 8;                         // of which one pass over the share sums

@@ -438,5 +438,57 @@ __device__ int read_winner(const unsigned long long* slots, unsigned long long e
   return aborting ? -1 : int(kIndexMask - (m & kIndexMask));
 }
 
+// The two-word form of publish_argmax and read_winner, for kernels that predict
+// the next winner (at most 64 columns a block): the block's best key in word 0
+// of its slot and its second-best in word 1, each with the epoch bit.
+__device__ __forceinline__ void publish_rows(const long long* sG, const unsigned char* ssel, int lo, int cnt, int S,
+                                             unsigned long long* slot, unsigned long long epoch) {
+  if (threadIdx.x >= 64) return;
+  const unsigned long long mine = column_key(sG, ssel, lo, threadIdx.x, cnt, S);
+  const unsigned long long k1 = wave_max_u64(mine);
+  const unsigned long long k2 = wave_max_u64(mine == k1 ? kNoCandidate : mine);
+  if (threadIdx.x < 2) put(slot + threadIdx.x, (threadIdx.x ? k2 : k1) | epoch);
+}
+
+// read_winner for two-word slots: thread i < nb polls both words of block
+// i's slot and stores them (epoch bits cleared) in sk1 and sk2.  Returns the
+// winner's index, -1 when the launch is aborting.
+__device__ int read_winner_rows(const unsigned long long* slots, unsigned long long epoch, int nb, unsigned int* abort,
+                                unsigned int limit, unsigned long long* su, int* sflag, unsigned long long* sk1,
+                                unsigned long long* sk2) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  unsigned long long best = 0ull;
+  if (tid == 0) *sflag = 0;
+  __syncthreads();
+  if (tid < nb) {
+    const unsigned long long* p = slots + size_t(tid) * kSlotStride;
+    bool done = false;
+    for (unsigned int spins = 0; !done; ++spins) {
+      const unsigned long long x0 = get(p), x1 = get(p + 1);
+      if ((x0 & kEpoch) == epoch && (x1 & kEpoch) == epoch) {
+        best = x0 & ~kEpoch;
+        sk1[tid] = best;
+        sk2[tid] = x1 & ~kEpoch;
+        done = true;
+      } else {
+        if (give_up(spins, limit, abort)) {
+          *sflag = 1;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+    }
+  }
+  best = wave_max_u64(best);
+  if (lane == 0) su[w] = best;
+  __syncthreads();
+  unsigned long long m = su[0];
+#pragma unroll
+  for (int q = 1; q < kWaves; ++q) m = su[q] > m ? su[q] : m;
+  const bool aborting = *sflag != 0;
+  __syncthreads();
+  return aborting ? -1 : int(kIndexMask - (m & kIndexMask));
+}
+
 }  // namespace
 }  // namespace cp

@@ -1902,7 +1902,7 @@ __global__ __launch_bounds__(kBlock) void inc_scale_kernel(IncDev a, int* scale)
 // Step-0 gains, every row at b = c0, split over a grid of (column strip,
 // row range) blocks so that the pass runs with many more waves in flight than
 // the greedy's one block per compute unit: block (b, p) sums rows
-// [p R, (p + 1) R) of columns [b W, (b + 1) W) into part[p][column], 64-bit
+// [p R, (p + 1) R) of columns [64 b, 64 b + 64) into part[p][column], 64-bit
 // fixed point, four waves adding in wave order.  A round covers 64 rows, 16
 // per wave.  With WT the round's 64 x 64 tile also goes to T through LDS:
 // lane `col` of a wave holds C_tm[j0 .. j0 + 16)[col], i.e. a piece of row
@@ -1913,6 +1913,7 @@ __global__ __launch_bounds__(kBlock) void inc_scale_kernel(IncDev a, int* scale)
 constexpr int kPassThreads = 256;
 constexpr int kPassWaves = kPassThreads / 64;
 constexpr int kPassRows = 16;
+constexpr int kPassCols = 64;                       // whatever W the greedy has: a lane a column
 constexpr int kPassTile = kPassWaves * kPassRows;   // rows per round
 constexpr int kPassLd = kPassTile + 4;               // LDS row of the tile: 16-byte aligned, banks spread
 
@@ -1923,7 +1924,7 @@ __host__ __device__ __forceinline__ int pass_rows(int n, int P) {
 template <bool WT, bool CHECK>
 __global__ __launch_bounds__(kPassThreads) void inc_first_pass_kernel(IncDev a, long long* part) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int lo = blockIdx.x * a.W, cnt = max(0, min(a.n, lo + a.W) - lo);
+  const int lo = blockIdx.x * kPassCols, cnt = min(a.n - lo, kPassCols);
   const int R = pass_rows(a.n, a.P), r0 = blockIdx.y * R, r1 = min(a.n, r0 + R);
   const int S = *a.scale;
   __shared__ long long red[kPassThreads];
@@ -2168,19 +2169,20 @@ IncDev inc_dev(const SgsParams& p, char* w, int nb, int W, bool rows) {
 }
 
 // The scale and the step-0 pass of one scene, ahead of the greedy's launch.
-hipError_t launch_first_pass(const IncDev& a, int nb, hipStream_t stream) {
+hipError_t launch_first_pass(const IncDev& a, hipStream_t stream) {
   inc_scale_kernel<<<1, kBlock, 0, stream>>>(a, const_cast<int*>(a.scale));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   long long* part = const_cast<long long*>(a.part);
+  const dim3 grid((a.n + kPassCols - 1) / kPassCols, a.P);
   if (a.T && (a.abort_init & 2u))
-    inc_first_pass_kernel<true, true><<<dim3(nb, a.P), kPassThreads, 0, stream>>>(a, part);
+    inc_first_pass_kernel<true, true><<<grid, kPassThreads, 0, stream>>>(a, part);
   else if (a.abort_init & 2u)
-    inc_first_pass_kernel<false, true><<<dim3(nb, a.P), kPassThreads, 0, stream>>>(a, part);
+    inc_first_pass_kernel<false, true><<<grid, kPassThreads, 0, stream>>>(a, part);
   else if (a.T)
-    inc_first_pass_kernel<true, false><<<dim3(nb, a.P), kPassThreads, 0, stream>>>(a, part);
+    inc_first_pass_kernel<true, false><<<grid, kPassThreads, 0, stream>>>(a, part);
   else
-    inc_first_pass_kernel<false, false><<<dim3(nb, a.P), kPassThreads, 0, stream>>>(a, part);
+    inc_first_pass_kernel<false, false><<<grid, kPassThreads, 0, stream>>>(a, part);
   return hipGetLastError();
 }
 
@@ -2241,7 +2243,7 @@ hipError_t run_incremental(const SgsParams& p, bool compact, const SgsFused* fus
   if (lists && (e = fits(list_kernel(W), kListLds, kListBlock)) != hipSuccess) return e;
   sgs_inc_init_kernel<<<std::min(1024, (std::max(p.n, p.k) + 255) / 256), 256, 0, stream>>>(a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (!fused && (e = launch_first_pass(a, nb, stream)) != hipSuccess) return e;
+  if (!fused && (e = launch_first_pass(a, stream)) != hipSuccess) return e;
   if (early) {
     void* eargs[] = {&a};
     if ((e = hipLaunchCooperativeKernel(early_kernel(W), dim3(nb), dim3(kBlock), eargs, lds, stream)) != hipSuccess)
@@ -2391,7 +2393,7 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
   for (int s = 0; s < count; ++s) {
     sgs_inc_init_kernel<<<std::min(1024, (std::max(p[s].n, p[s].k) + 255) / 256), 256, 0, stream>>>(b.scene[s]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = launch_first_pass(b.scene[s], b.g0[s + 1] - b.g0[s], stream)) != hipSuccess) return e;
+    if ((e = launch_first_pass(b.scene[s], stream)) != hipSuccess) return e;
   }
   void* args[] = {&b};
   if (early) {

@@ -361,6 +361,12 @@ __device__ __forceinline__ long long key_gain_floor(unsigned long long key, int 
   return max(0ll, G - (G >> 52) - 1);
 }
 
+// The best costs that the rows kernel hands to the list phase, ldt floats
+// beside the lists' lengths: both lie in the compact form's change lists
+// (16 (n + kMaxBlocks) bytes), which the rows form does not use.
+__host__ __device__ __forceinline__ size_t llen_words(int n) { return (size_t(n) + 63) / 64 * 64; }
+__device__ __forceinline__ float* list_ho_b(const IncDev& a) { return reinterpret_cast<float*>(a.llen + llen_words(a.n)); }
+
 constexpr int kTrackMax = 256;   // hits of a step that still tracks the runner-up
 
 // The step-0 gains of a block's columns [lo, lo + cnt) from the P partial
@@ -784,14 +790,18 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
     a.step_obj[obj_step] = fx_to_double(L, S);
   }
   // Hand the state over to the list phase, which starts with an exchange of
-  // its own.
+  // its own.  The best costs go to a place of their own: a launch that resumed
+  // with one step left, or two of which the second was predicted, waits for no
+  // exchange after its first, whose candidates the early kernel published, so
+  // block 0 can be here before a late block has read ho_b.
   if (a.k_end < a.k) {
     for (int i = tid; i < cnt; i += kBlock) {
       a.ho_gain[lo + i] = sG[i];
       a.ho_sel[lo + i] = ssel[i];
     }
     if (blk == 0) {
-      for (int j = tid; j < a.ldt; j += kBlock) a.ho_b[j] = sball[j];
+      float* bo = list_ho_b(a);
+      for (int j = tid; j < a.ldt; j += kBlock) bo[j] = sball[j];
       if (tid == 0) {
         long long L = 0;
 #pragma unroll
@@ -1192,7 +1202,7 @@ __global__ __launch_bounds__(256) void list_build_kernel(IncDev a) {
   const int c = blockIdx.x * 4 + w;
   if (c >= a.n) return;
   const f32x4* row = reinterpret_cast<const f32x4*>(a.T + size_t(c) * a.ldt);
-  const f32x4* bb = reinterpret_cast<const f32x4*>(a.ho_b);
+  const f32x4* bb = reinterpret_cast<const f32x4*>(list_ho_b(a));
   const int nch = a.ldt / kRowChunk;
   const unsigned long long lt = (1ull << lane) - 1ull;
   int m = 0;
@@ -1352,8 +1362,9 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
   __shared__ unsigned short slen[64 * NG];                          // own candidates' pairs, 65535 for more
   const int S = *a.scale;
 
+  const float* hb = list_ho_b(a);
   for (int j = tid; j < a.ldt; j += kListBlock) {
-    sball[j] = a.ho_b[j];
+    sball[j] = hb[j];
     if (v_lds) sv[j] = j < a.n ? a.v[j] : 0.f;
   }
   for (int i = tid; i < list_off_words(a.n); i += kListBlock) soffw[i] = 0u;
@@ -2162,7 +2173,7 @@ IncDev inc_dev(const SgsParams& p, char* w, int nb, int W, bool rows) {
     a.lcap = own ? kListCap : std::min(kListCap, a.ldt / 2);
     a.lstride = own ? size_t(kListCap) : size_t(a.ldt) / 2;
     a.lent = list_ent(p.n, W);
-    a.llen = reinterpret_cast<unsigned int*>(w + L.list);   // the compact form's change lists are not in use
+    a.llen = reinterpret_cast<unsigned int*>(w + L.list);   // and the best costs handed over (list_ho_b)
     a.k_end = list_step(p.n);
   }
   return a;

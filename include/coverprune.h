@@ -40,9 +40,10 @@
  *     distinct workspaces and streams may run concurrently.
  *   - Waits between the blocks of one launch are bounded.  The greedy
  *     selection calls (sgs_select, sgs_select_batch, sgs_local_select, the
- *     greedy of prune, and sgs_literal_select up to n = 2048 and k = 256
- *     without a trajectory to follow) run persistent launches whose blocks wait for each
- *     other (lite_select has no such waits: ordinary launches only).  A wait
+ *     greedy of prune, and sgs_literal_select up to n = 2048, k = 256 and
+ *     16384 rounds without a trajectory to follow) run persistent launches
+ *     whose blocks wait for each other (lite_select has no such waits:
+ *     ordinary launches only).  A wait
  *     that has polled for about a second (far beyond any legitimate wait: a launch
  *     starved of compute units, or a broken device) gives up, every block of
  *     the launch leaves, and every entry of `selected` is set to -1, which is
@@ -404,9 +405,9 @@ cp_status coverprune_sgs_local_select(const float* cost, int64_t n, const float*
  * sums in a fixed order (deterministic); E underflows to 0 where
  * C / epsilon exceeds about 708, so epsilon should stay above max C / 700.
  * Each step costs `rounds` passes over an n x l matrix and one pass over the
- * cost: separate launches, or, for n <= 2048 and k <= 256 without `follow` on
- * a stream that is not being captured, one persistent launch that keeps both
- * on the compute units.
+ * cost: separate launches, or, for n <= 2048, k <= 256 and at most 16384
+ * rounds without `follow` on a stream that is not being captured, one
+ * persistent launch that keeps both on the compute units.
  *
  *   cost, n, capacity: as for coverprune_sgs_select (every retained token must
  *             reach some target at finite E, e.g. C(s, s) = 0 as the FST cost has)

@@ -259,7 +259,8 @@ __global__ void lit_objective_sum_kernel(LitDev p) {
 
 // ---------------------------------------------------------------------------
 // The same greedy in one cooperative launch, for scenes whose E fits in
-// registers and whose cost in LDS (n <= kPersN, k <= kPersK; no trajectory to follow).
+// registers and whose cost in LDS (n <= kPersN, k <= kPersK, rounds <= kPersRounds; no
+// trajectory to follow).
 //
 // A scaling round is two dependent passes over a small matrix (3.4 MB at
 // n = 2048, k = 205), and 10 250 rounds follow one another: as two launches a
@@ -283,6 +284,11 @@ constexpr int kPersSolvers = kPersN / kPersRows;      // 32
 constexpr int kPersScore = 8;                         // rows of the cost a block holds, and candidates it adds up
 constexpr int kPersBlocks = kPersN / kPersScore;      // 256
 constexpr int kPersChunks = kPersK / 64;              // columns a lane holds
+// The scoring blocks poll through a whole solve, `rounds` exchanges of 4.4 us,
+// within the limit of about a second that bounds every wait: up to this many
+// rounds (72 ms) a solve stays far below it.  Longer ones take the separate
+// launches, which wait for nothing.
+constexpr int kPersRounds = 16384;
 
 struct LitPers {
   const float* C;
@@ -725,7 +731,7 @@ size_t lit_pers_bytes(int64_t n) {
 // not being captured (the separate launches can be); *done says so.
 hipError_t try_persistent(const LiteralParams& q, hipStream_t stream, bool* done) {
   *done = false;
-  if (q.follow || !lit_pers_serves(q.n, q.k) || q.workspace_bytes < lit_pers_bytes(q.n)) return hipSuccess;
+  if (q.follow || q.rounds > kPersRounds || !lit_pers_serves(q.n, q.k) || q.workspace_bytes < lit_pers_bytes(q.n)) return hipSuccess;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
     (void)hipGetLastError();

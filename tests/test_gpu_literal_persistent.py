@@ -46,3 +46,21 @@ def test_persistent_that_gives_up(monkeypatch):
     monkeypatch.delenv("COVERPRUNE_TEST_ABORT")
     r = cp.sgs_literal_select(cost, cap, 20, epsilon=0.05, rounds=10)
     assert int(r.selected.min()) >= 0
+
+
+def test_long_solves_take_the_separate_launches(monkeypatch):
+    # The persistent launch's scoring blocks wait through a whole solve, so past
+    # 16384 rounds the separate launches serve, which wait for nothing: a launch
+    # that is made to give up at its first unmet wait tells the two apart.
+    import paper_2608_13226_amd as cp
+    cost, cap = _case(64, 2)
+    monkeypatch.setenv("COVERPRUNE_TEST_ABORT", "1")
+    for rounds in (16384, 16385):
+        print(f"literal rounds={rounds}", flush=True)
+        r = cp.sgs_literal_select(cost, cap, 2, epsilon=0.05, rounds=rounds)
+        torch.cuda.synchronize()
+        assert (int(r.selected.min()) >= 0) == (rounds > 16384)
+    monkeypatch.delenv("COVERPRUNE_TEST_ABORT")
+    one = cp.sgs_literal_select(cost, cap, 2, epsilon=0.05, rounds=16384)
+    torch.cuda.synchronize()
+    assert one.selected.tolist() == r.selected.tolist()

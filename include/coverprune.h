@@ -192,8 +192,11 @@ cp_status coverprune_fst_capacity(const void* feats, cp_dtype dtype, int64_t n, 
  *             c0 * max v < 2^(52 - S); costs are taken in [0, c0]) and summed
  *             exactly in 64-bit integers, so picks can differ from the dense
  *             sweep's float64 sums only between gains within rounding of
- *             each other.  Gains compare to 2^-31 relative
- *             (below that the smaller index wins).
+ *             each other.  Candidates of one group of ceil(n / ceil(n / 64))
+ *             consecutive tokens (ceil(n / 256) above n = 16384; on a device
+ *             of 256 compute units) compare by their exact gains, candidates
+ *             of different groups to 2^-31 relative (below that the smaller
+ *             index wins).
  *             For n <= 32768 every compute unit keeps all n best costs and
  *             finds the targets a pick improves itself, from the pick's row
  *             of a source-major copy of the cost that the first pass writes
@@ -282,7 +285,9 @@ cp_status coverprune_prune(const void* feats, cp_dtype dtype, int64_t n, int64_t
  * cooperative launch: scene s gets its own group of blocks (one block per
  * compute unit in all, groups balanced by tokens per block) and its own
  * exchanges, so each scene's result is what coverprune_sgs_select with
- * CP_SGS_INCREMENTAL computes for it alone.
+ * CP_SGS_INCREMENTAL computes for it alone (its groups of exact comparison
+ * can be wider, where the scenes together have more than 64 tokens per compute
+ * unit, which matters only for gains equal to 2^-31 relative).
  * The call takes as long as its slowest scene.
  *
  *   scenes    host array of `count` scene descriptions (read during the call

@@ -98,7 +98,7 @@ __device__ __forceinline__ void inc_body(const IncDev& a, int blk, int nb) {
     if (tid < kWaves) sLw[tid] = tid == 0 ? L0 : 0;
   }
 
-  publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), su);
+  publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), su);
 
   for (int step = 0; step < a.k; ++step) {
     // Some block has a candidate while unchosen columns remain; the clamp
@@ -264,7 +264,7 @@ __device__ __forceinline__ void inc_body(const IncDev& a, int blk, int nb) {
 
     // 4. This block's candidate for the next step.
     if (step + 1 < a.k)
-      publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, (step + 1) & 1, blk),
+      publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, (step + 1) & 1, blk),
                      epoch_of(step + 1), su);
   }
   __syncthreads();
@@ -419,7 +419,7 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
   __shared__ long long red[kBlock];
   __shared__ long long sg[kWaves];
   __shared__ unsigned long long su[kWaves];
-  __shared__ int sflag;
+  __shared__ int sflag[2];
   __shared__ int lj[kCapR];                    // hit list: target
   __shared__ float lbo[kCapR];                 // old best cost
   __shared__ float lbn[kCapR];                 // new best cost
@@ -430,7 +430,7 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
   // slot words of the last exchange and the waves' parts of the runner-up's
   // change in the step.
   constexpr bool kSpec = NG == 1;
-  __shared__ unsigned long long sk1[kSpec ? kMaxBlocks : 1], sk2[kSpec ? kMaxBlocks : 1];
+  __shared__ unsigned long long sk1[kSpec ? kMaxBlocks : 1], sk2[kSpec ? kMaxBlocks : 1], sk3[kSpec ? kMaxBlocks : 1];
   __shared__ long long sdr[kWaves];
 
   if (unfit(a)) return;
@@ -475,9 +475,9 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
   int xc = resume ? int(a.ho_misc[1]) : 0;
   if (!resume) {
     if (kSpec)
-      publish_rows(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0));
+      publish_rows<true>(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0));
     else
-      publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), su);
+      publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), su);
   }
 
   const int nch = a.ldt / kRowChunk;
@@ -497,9 +497,8 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
       __syncthreads();
       tw = tpred;
     } else {
-      tw = kSpec ? read_winner_rows(cand_slot(a.cand, xc & 1, 0), epoch_of(xc), nb, a.abort, a.poll_limit, su,
-                                    &sflag, sk1, sk2)
-                 : read_winner(cand_slot(a.cand, xc & 1, 0), epoch_of(xc), nb, a.abort, a.poll_limit, su, &sflag);
+      tw = kSpec ? read_winner_rows<true>(a, cand_slot(a.cand, xc & 1, 0), epoch_of(xc), nb, su, sflag, sk1, sk2, sk3)
+                 : read_winner(cand_slot(a.cand, xc & 1, 0), epoch_of(xc), nb, a.abort, a.poll_limit, su, sflag);
       ++xc;
     }
     if (tw < 0) break;
@@ -775,9 +774,9 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
     }
     if (step + 1 < a.k_end && !next) {
       if (kSpec)
-        publish_rows(sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc));
+        publish_rows<true>(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc));
       else
-        publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc), su);
+        publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc), su);
     }
     predicted = next;
     tpred = rn;
@@ -870,8 +869,8 @@ __device__ __forceinline__ void early_body(const IncDev& a, int blk, int nb) {
   unsigned char* ssel = reinterpret_cast<unsigned char*>(sball + a.ldt);   // [W] chosen columns
   __shared__ long long red[NG * kBlock];
   __shared__ unsigned long long su[kWaves];
-  __shared__ unsigned long long sk1[NG == 1 ? kMaxBlocks : 1], sk2[NG == 1 ? kMaxBlocks : 1];
-  __shared__ int sflag;
+  __shared__ unsigned long long sk1[NG == 1 ? kMaxBlocks : 1], sk2[NG == 1 ? kMaxBlocks : 1], sk3[NG == 1 ? kMaxBlocks : 1];
+  __shared__ int sflag[2];
   __shared__ int schunk[kEarlyMaxN / kRowChunk];     // hits per chunk of the winner's row, then their offsets
   __shared__ int stot;
   __shared__ int sj[kEarlyShare];                     // the block's share: target, old and new best cost,
@@ -891,9 +890,9 @@ __device__ __forceinline__ void early_body(const IncDev& a, int blk, int nb) {
   }
   auto publish = [&](int x) {
     if (NG == 1)
-      publish_rows(sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x));
+      publish_rows<true>(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x));
     else
-      publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x), su);
+      publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x), su);
   };
   publish(0);
 
@@ -903,8 +902,8 @@ __device__ __forceinline__ void early_body(const IncDev& a, int blk, int nb) {
   int xc = 0;
   for (int step = 0; step < k_stop; ++step) {
     const unsigned long long* slots = cand_slot(a.cand, xc & 1, 0);
-    const int tw = NG == 1 ? read_winner_rows(slots, epoch_of(xc), nb, a.abort, a.poll_limit, su, &sflag, sk1, sk2)
-                           : read_winner(slots, epoch_of(xc), nb, a.abort, a.poll_limit, su, &sflag);
+    const int tw = NG == 1 ? read_winner_rows<true>(a, slots, epoch_of(xc), nb, su, sflag, sk1, sk2, sk3)
+                           : read_winner(slots, epoch_of(xc), nb, a.abort, a.poll_limit, su, sflag);
     ++xc;
     if (tw < 0) return;
     const int t = min(tw, a.n - 1);
@@ -1040,17 +1039,17 @@ __device__ __forceinline__ void early_body(const IncDev& a, int blk, int nb) {
     if (nsh > 0 && tid == 0) put(lens_slot(a.lens, blk), (unsigned long long)(step + 1));
 
     // Every share's sums, once its block has raised its flag for the step.
-    if (tid == 0) sflag = 0;
+    if (tid == 0) sflag[0] = 0;
     __syncthreads();
     if (tid < nshare) {
       unsigned long long f;
       const unsigned long long want = (unsigned long long)(step + 1);
       if (!wait_slot(lens_slot(a.lens, tid), a.abort, a.poll_limit, [want](unsigned long long v) { return v == want; },
                      f))
-        sflag = 1;
+        sflag[0] = 1;
     }
     __syncthreads();
-    if (sflag) return;
+    if (sflag[0]) return;
     {
       // All of a thread's loads are issued before any is used (a row past
       // nshare, or a column past cnt, is read from a valid address and not
@@ -1241,16 +1240,16 @@ __global__ __launch_bounds__(256) void list_build_kernel(IncDev a) {
 __device__ __forceinline__ int gain_bits(long long g) { return g < 0 ? -1 : __float_as_int(float(g)); }
 __device__ __forceinline__ long long lane_i64(long long x, int l) { return (long long)lane_u64((unsigned long long)x, l); }
 
-// The kPub best unchosen columns of the block, by (gain_key, smaller index),
-// and the gain of the best one left out.  Every thread counts, for one column, the columns
+// The kPub first unchosen columns of the block in the order of candidates,
+// and the gain of the next one, left out.  Every thread counts, for one column, the columns
 // of its part that come before it (a maximum after another over one wave took
 // four times as long); wave 0 publishes.  Words kListWord + r hold the gains,
 // the next the own indices (8 bits each), then the rest's gain and the
 // lists' lengths (12 bits each).  64 NG columns at most; starts and ends a
 // phase between barriers of the whole block.
 template <int NG>
-__device__ __forceinline__ void publish_list(const unsigned long long* sG, const unsigned char* ssel,
-                                             const unsigned short* slen, int cnt, int* srank, int* stop,
+__device__ __forceinline__ void publish_list(const IncDev& a, const unsigned long long* sG, const unsigned char* ssel,
+                                             const unsigned short* slen, int lo, int cnt, int* srank, int* stop,
                                              unsigned long long* slot, unsigned long long epoch) {
   constexpr int kCols = 64 * NG, kParts = kListBlock / kCols;
   const int tid = threadIdx.x;
@@ -1258,15 +1257,26 @@ __device__ __forceinline__ void publish_list(const unsigned long long* sG, const
   if (tid < kPub + 1) stop[tid] = -1;
   {
     const int per = (cnt + kParts - 1) / kParts, m1 = min(cnt, (part + 1) * per);
-    // Chosen columns count as key 0.
-    const unsigned long long u = i < cnt && !ssel[i] ? gain_key((long long)sG[i]) : 0ull;
+    // Own columns from `bnd` on lie in the next group.  Chosen columns count
+    // as gain -1 (key 0).
+    const int bnd = (group_of(a, lo) + 1) * a.grp - lo;
+    const long long g = i < cnt && !ssel[i] ? (long long)sG[i] : -1;
     int before = 0;
-    for (int m = part * per; m < m1; ++m) {
-      const unsigned long long x = ssel[m] ? 0ull : gain_key((long long)sG[m]);
-      before += x + (m < i ? 1 : 0) > u ? 1 : 0;
+    if (bnd >= cnt) {
+      for (int m = part * per; m < m1; ++m) {
+        const long long x = ssel[m] ? -1 : (long long)sG[m];
+        before += x + (m < i ? 1 : 0) > g ? 1 : 0;
+      }
+    } else {
+      const unsigned long long u = gain_key(g);
+      for (int m = part * per; m < m1; ++m) {
+        const long long x = ssel[m] ? -1 : (long long)sG[m];
+        const bool same = (m < bnd) == (i < bnd);
+        before += (same ? x : (long long)gain_key(x)) + (m < i ? 1 : 0) > (same ? g : (long long)u) ? 1 : 0;
+      }
     }
     // srank[i] was left at zero by the previous call.
-    if (i < cnt && u) atomicAdd(&srank[i], before);
+    if (i < cnt && g >= 0) atomicAdd(&srank[i], before);
   }
   lds_barrier();
   if (tid < kCols) {
@@ -1527,7 +1537,7 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
 
   int step = a.k_begin;
   int gap = 1 << 20;                                                // the last round's threshold below its best
-  publish_list<NG>(sG, ssel, slen, cnt, srank, stop5, cand_slot(a.cand, 0, blk), epoch_of(0));
+  publish_list<NG>(a, sG, ssel, slen, lo, cnt, srank, stop5, cand_slot(a.cand, 0, blk), epoch_of(0));
   for (int xc = 0; step < a.k; ++xc) {
     // The exchange: a wave reads eight slots per load, eight lanes each.
     {
@@ -1679,6 +1689,7 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
       const bool mine = lane < ns;
       const int myidx = mine ? sidx[lane & (kSet - 1)] : INT_MAX;
       const int mylen = mine ? slist[lane & (kSet - 1)] : 0;
+      const int mygrp = group_of(a, myidx);
       const int mych = (mylen + 63) >> 6;
       const int myend = wave_scan_incl(mych), mystart = myend - mych;
       const int nch = __builtin_amdgcn_readlane(myend, 63);
@@ -1719,8 +1730,8 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
       int nh = 0;                                                   // hits this wave has listed
       lds_barrier();   // every wave has read the best costs before the first pick lowers any
       for (;; ++np) {
-        // The best of the set, the same in every wave: the largest high word
-        // of the keys, then (rarely) the low word, then the smallest index.
+        // The first of the set, the same in every wave: the largest high word
+        // of the keys, then (rarely) the low word, then first_of.
         const long long gl = mine && !((done >> (lane & 31)) & 1u) ? (long long)sset[lane & (kSet - 1)] : -1;
         const unsigned long long u = gain_key(gl);
         const unsigned hm = half_max_u32(unsigned(u >> kKeyLow));
@@ -1728,11 +1739,7 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
         if (__popcll(tie) > 1) {
           const unsigned lm = half_max_u32(unsigned(u >> kKeyLow) == hm ? unsigned(u) & kKeyLowMask : 0u);
           tie &= __ballot((unsigned(u) & kKeyLowMask) == lm);
-          if (__popcll(tie) > 1) {
-            const bool in = (tie >> lane) & 1ull;
-            const int im = wave_min_i32(in ? myidx : INT_MAX);
-            tie = __ballot(in && myidx == im);
-          }
+          if (__popcll(tie) > 1) tie = 1ull << first_of(tie, mygrp, gl, myidx);
         }
         const int slot = __builtin_ctzll(tie);
         const long long g = lane_i64(gl, slot);
@@ -1810,23 +1817,36 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
     }
     if (np == 0) {
       // The best candidate of all, alone, from its list or its row of T.
-      unsigned long long kb = 0ull;
-      int ib = INT_MAX, bb = 0;
+      unsigned long long kb[4], kmax = 0ull;
+      int ib[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int b = lane + 64 * q;
-        const unsigned long long key = gain_key(word_gain(sgw[0][b]));
-        if (key > kb) {                                             // equal keys keep the lower block
-          kb = key;
-          bb = b;
-          ib = b * a.W + int(sgi[b] & 0xffu);
+        kb[q] = gain_key(word_gain(sgw[0][b]));
+        ib[q] = b * a.W + int(sgi[b] & 0xffu);
+        kmax = max(kmax, kb[q]);
+      }
+      const unsigned long long top = wave_max_u64(kmax);
+      if (top == 0ull) break;                                       // never with a candidate left
+      // Of the blocks' best ones with that key: the lowest group's (it holds
+      // the smallest index), there the largest gain, then the smallest index.
+      int im = INT_MAX;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) im = min(im, kb[q] == top ? ib[q] : INT_MAX);
+      const int gm = group_of(a, wave_min_i32(im));
+      long long gx = -1;
+      int bx = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {                                 // increasing index
+        const long long gq = word_gain(sgw[0][lane + 64 * q]);
+        if (kb[q] == top && group_of(a, ib[q]) == gm && gq > gx) {
+          gx = gq;
+          bx = lane + 64 * q;
         }
       }
-      const unsigned long long top = wave_max_u64(kb);
-      if (top == 0ull) break;                                       // never with a candidate left
-      const int im = wave_min_i32(kb == top ? ib : INT_MAX);
-      const int wb = __builtin_amdgcn_readlane(bb, __builtin_ctzll(__ballot(kb == top && ib == im)));
-      const int t = min(im, a.n - 1);
+      const unsigned long long gt = wave_max_u64((unsigned long long)(gx + 1));
+      const int wb = wave_min_i32((unsigned long long)(gx + 1) == gt ? bx : INT_MAX);
+      const int t = min(wb * a.W + int(sgi[wb] & 0xffu), a.n - 1);
       const long long gb = word_gain(sgw[0][wb]);
       const int len = __builtin_amdgcn_readfirstlane(int(sgl[wb]) & 0xfff);
       const bool listed = len <= a.lcap;
@@ -1868,7 +1888,7 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
     }
     __syncthreads();
     if (step + np < a.k)
-      publish_list<NG>(sG, ssel, slen, cnt, srank, stop5, cand_slot(a.cand, (xc + 1) & 1, blk), epoch_of(xc + 1));
+      publish_list<NG>(a, sG, ssel, slen, lo, cnt, srank, stop5, cand_slot(a.cand, (xc + 1) & 1, blk), epoch_of(xc + 1));
     if (w == 1 && blk == 0) {
       unsigned long long L = sL;
       for (int i = 0; i < np; ++i) L += lane >= i ? sobj[i] : 0ull;
@@ -2062,7 +2082,7 @@ constexpr int kShortN = 2048, kShortK = 20;
 bool short_greedy(int64_t n, int64_t k) { return n <= kShortN && k <= kShortK; }
 int inc_blocks(int64_t n, int64_t k, int cus, bool compact, bool* rows) {
   const int nb = blocks_for(n, cus, kRowsPer);
-  *rows = !compact && !short_greedy(n, k) && use_rows(n, int((n + nb - 1) / nb));
+  *rows = !compact && !short_greedy(n, k) && use_rows(n, cols_for(n, nb));
   return *rows ? nb : blocks_for(n, cus, 64);
 }
 
@@ -2125,7 +2145,10 @@ IncLayout inc_layout(int64_t n, int64_t k, bool compact) {
 }
 size_t inc_bytes(int64_t n, int64_t k, bool compact) { return inc_layout(n, k, compact).total; }
 
-IncDev inc_dev(const SgsParams& p, char* w, int nb, int W, bool rows) {
+// nb: blocks; W64: the columns of one of a block per 64 tokens, whose gains compare
+// exactly whatever the form's own split (a wider split is a group itself).
+IncDev inc_dev(const SgsParams& p, char* w, int nb, int W64, bool rows) {
+  const int W = cols_for(p.n, nb);
   const Layout L = layout(p.n, p.k);
   IncDev a{};
   a.C = p.cost;
@@ -2146,6 +2169,8 @@ IncDev inc_dev(const SgsParams& p, char* w, int nb, int W, bool rows) {
   a.abort_init = wp.preset;
   a.W = W;
   a.w_magic = w_magic_of(W);
+  a.grp = std::max(W, W64);
+  a.g_magic = w_magic_of(a.grp);
   const IncLayout M = inc_layout(p.n, p.k, !rows);
   a.T = rows ? reinterpret_cast<float*>(w + M.T) : nullptr;
   a.ldt = rows ? rows_ldt(p.n) : 0;
@@ -2232,12 +2257,12 @@ hipError_t run_incremental(const SgsParams& p, bool compact, const SgsFused* fus
   if (e != hipSuccess) return e;
   bool rows = false;
   const int nb = inc_blocks(p.n, p.k, cus, compact, &rows);
-  const int W = (p.n + nb - 1) / nb;
+  const int W = cols_for(p.n, nb);
   const void* kernel = rows ? rows_kernel(p.n, W) : reinterpret_cast<const void*>(sgs_inc_kernel);
   const size_t lds = rows ? lds_rows(W, p.n) : lds_for(W);
   if ((e = fits(kernel, lds)) != hipSuccess) return e;
 
-  IncDev a = inc_dev(p, static_cast<char*>(p.workspace), nb, W, rows);
+  IncDev a = inc_dev(p, static_cast<char*>(p.workspace), nb, cols_for(p.n, blocks_for(p.n, cus, 64)), rows);
   if (fused) {
     a.part = fused->part;
     a.P = fused->P;
@@ -2290,8 +2315,7 @@ hipError_t launch_sgs_checked(const SgsParams& p, const unsigned int** unfit, hi
 bool sgs_fused_fits(int64_t n) {
   int cus = 0;
   if (device_cus(&cus) != hipSuccess || n < 64 || n % 64 != 0) return false;
-  const int nb = blocks_for(n, cus, kRowsPer);
-  return use_rows(n, int((n + nb - 1) / nb));
+  return use_rows(n, cols_for(n, blocks_for(n, cus, kRowsPer)));
 }
 
 size_t sgs_fused_workspace_bytes(int64_t n, int64_t k) {
@@ -2303,7 +2327,7 @@ hipError_t sgs_fused_prepare(const SgsParams& p, SgsFused* f, hipStream_t stream
   hipError_t e = hipError_t(device_cus(&cus));
   if (e != hipSuccess) return e;
   const int nb = blocks_for(p.n, cus, kRowsPer);
-  IncDev a = inc_dev(p, static_cast<char*>(p.workspace), nb, (p.n + nb - 1) / nb, true);
+  IncDev a = inc_dev(p, static_cast<char*>(p.workspace), nb, cols_for(p.n, nb), true);
   f->T = a.T;
   f->ldt = a.ldt;
   f->part = reinterpret_cast<long long*>(static_cast<char*>(p.workspace) + inc_bytes(p.n, p.k, false));
@@ -2323,6 +2347,27 @@ size_t sgs_inc_batch_workspace_bytes(const int64_t* n, const int64_t* k, int cou
   return total;
 }
 
+// One block per compute unit in all: every scene starts with one, then the
+// scene with the most tokens per block gains one (up to its own cap of one
+// block per `per` tokens, at most kMaxBlocks) until the units run out.
+// Returns the blocks handed out.
+static int share_blocks(const SgsParams* p, int count, int cus, int per, int* nb) {
+  int used = count;
+  for (int s = 0; s < count; ++s) nb[s] = 1;
+  while (used < cus) {
+    int best = -1, bw = 0;
+    for (int s = 0; s < count; ++s)
+      if (nb[s] < blocks_for(p[s].n, cus, per) && cols_for(p[s].n, nb[s]) > bw) {
+        bw = cols_for(p[s].n, nb[s]);
+        best = s;
+      }
+    if (best < 0) break;
+    ++nb[best];
+    ++used;
+  }
+  return used;
+}
+
 hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool compact, void* workspace,
                                         hipStream_t stream) {
   if (count < 1 || count > kMaxBatch) return hipErrorInvalidValue;
@@ -2331,32 +2376,11 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
   if (e != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
   if (count > cus) return hipErrorInvalidValue;
-  // One block per compute unit in all: every scene starts with one, then the
-  // scene with the most tokens per block gains one (up to its own cap of one
-  // block per 64 tokens, at most kMaxBlocks) until the units run out.
   bool rows = false;
   for (int s = 0; s < count; ++s) rows = rows || (!compact && !short_greedy(p[s].n, p[s].k));
-  int nb[kMaxBatch], cap[kMaxBatch];
-  int used = count;
-  for (int s = 0; s < count; ++s) {
-    nb[s] = 1;
-    cap[s] = blocks_for(p[s].n, cus, rows ? kRowsPer : 64);
-  }
-  while (used < cus) {
-    int best = -1;
-    long long bw = 0;
-    for (int s = 0; s < count; ++s) {
-      if (nb[s] >= cap[s]) continue;
-      const long long w = (p[s].n + nb[s] - 1) / nb[s];
-      if (w > bw) {
-        bw = w;
-        best = s;
-      }
-    }
-    if (best < 0) break;
-    ++nb[best];
-    ++used;
-  }
+  int nb[kMaxBatch], nb64[kMaxBatch];
+  const int used = share_blocks(p, count, cus, rows ? kRowsPer : 64, nb);
+  share_blocks(p, count, cus, 64, nb64);
   // The rows form when every scene allows it (one form per launch) and one is
   // not short, with the early and list kernels for the scenes they serve.
   // A handful of picks does not pay for two more launches (three scenes of 256
@@ -2365,7 +2389,7 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
   for (int s = 0; s < count; ++s) lists = lists || (rows && p[s].k > kBatchListK);
   int wmax = 0, nmax = 0;
   for (int s = 0; s < count; ++s) {
-    const int W = (p[s].n + nb[s] - 1) / nb[s];
+    const int W = cols_for(p[s].n, nb[s]);
     rows = rows && use_rows(p[s].n, W);
     early = early || early_for(p[s].n, W);
     lists = lists && p[s].n <= kListMaxN && W <= kRowsMaxW;
@@ -2380,9 +2404,9 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
   size_t lds = 0, off = 0;
   char* w = static_cast<char*>(workspace);
   for (int s = 0; s < count; ++s) {
-    const int W = (p[s].n + nb[s] - 1) / nb[s];
+    const int W = cols_for(p[s].n, nb[s]);
     IncDev& a = b.scene[s];
-    a = inc_dev(p[s], w + off, nb[s], W, rows);
+    a = inc_dev(p[s], w + off, nb[s], cols_for(p[s].n, nb64[s]), rows);
     if (!lists) {
       a.epart = nullptr;
       a.lists = nullptr;

@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
   __shared__ long long sg[kWaves];
   __shared__ double sd[kWaves];
   __shared__ unsigned long long su[kWaves];
-  __shared__ int sflag;
+  __shared__ int sflag[2];
   __shared__ long long sLw[kWaves];            // this block's objective part, one running share per wave
   __shared__ unsigned long long sk1[kMaxBlocks], sk2[kMaxBlocks];   // the last exchange's keys
   __shared__ long long sgr;                    // the next chain candidate's gain
@@ -206,9 +206,9 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
   const bool spec = a.W <= 64;
   auto publish = [&](int x) {
     if (spec)
-      publish_rows(sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x));
+      publish_rows<false>(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x));
     else
-      publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x), su);
+      publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x), su);
   };
   __syncthreads();
   local_gains();
@@ -238,8 +238,8 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
     int t = -1;
     if (!predicted) {
       const unsigned long long* slots = cand_slot(a.cand, xc & 1, 0);
-      const int tw = spec ? read_winner_rows(slots, epoch_of(xc), nb, a.abort, a.poll_limit, su, &sflag, sk1, sk2)
-                          : read_winner(slots, epoch_of(xc), nb, a.abort, a.poll_limit, su, &sflag);
+      const int tw = spec ? read_winner_rows<false>(a, slots, epoch_of(xc), nb, su, sflag, sk1, sk2, nullptr)
+                          : read_winner(slots, epoch_of(xc), nb, a.abort, a.poll_limit, su, sflag);
       ++xc;
       if (tw < 0) break;
       t = min(tw, a.n - 1);
@@ -457,6 +457,8 @@ hipError_t launch_sgs_local(const SgsParams& p, const int32_t* nbr, int g, hipSt
   a.abort_init = wp.preset;
   a.W = W;
   a.w_magic = w_magic_of(W);
+  a.grp = W;               // a block's columns: their exact gains compare
+  a.g_magic = a.w_magic;
   a.T = reinterpret_cast<float*>(w + Y.T);
   a.ldt = ldt;
   d.nbr = nbr;

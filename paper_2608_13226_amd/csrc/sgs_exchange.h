@@ -63,8 +63,10 @@ struct IncDev {
   unsigned int w_magic;       // floor(2^32 / W) + 1: block_of(c) = c / W by one high multiply
   float* T;                   // rows form only: [n][ldt] source-major copy, T[s][t] = C(s, t)
   int ldt;                    // its row stride, n rounded up to a whole 256-row chunk
+  unsigned int g_magic;       // floor(2^32 / grp) + 1: group_of(c) = c / grp
   const long long* part;      // incremental form: [P][n] step-0 gains summed over P row ranges
   int P;
+  int grp;                    // consecutive columns whose gains compare exactly (pack_key); at least W
   const int* scale;           // incremental form: the fixed-point exponent S
   // Rows schedule in several launches with a hand-over (see k_sgs_inc.hip):
   // the steps of this launch and the state handed from one to the next.
@@ -100,6 +102,7 @@ __device__ __forceinline__ bool unfit(const IncDev& a) { return (a.abort_init & 
 // 0 and column 0's block is 0.
 __device__ __forceinline__ int block_of(const IncDev& a, int c) { return int(__umulhi(unsigned(c), a.w_magic)); }
 inline unsigned int w_magic_of(int W) { return unsigned(0xffffffffu / unsigned(W)) + 1u; }
+__device__ __forceinline__ int group_of(const IncDev& a, int c) { return int(__umulhi(unsigned(c), a.g_magic)); }
 
 struct Layout {
   size_t list, lens, cand, ctrl, total;
@@ -111,6 +114,9 @@ size_t a256(size_t x) { return (x + 255) / 256 * 256; }
 int blocks_for(int64_t n, int cus, int per) {
   return int(std::max<int64_t>(1, std::min<int64_t>(std::min(cus, kMaxBlocks), (n + per - 1) / per)));
 }
+
+// Columns a block of nb.
+int cols_for(int64_t n, int nb) { return int((n + nb - 1) / nb); }
 
 // Sized for the largest grid (kMaxBlocks blocks of W = ceil(n / blocks) rows).
 Layout layout(int64_t n, int64_t k) {
@@ -134,11 +140,14 @@ __host__ __device__ __forceinline__ unsigned long long* lens_slot(unsigned long 
   return lens + size_t(b) * kSlotStride;
 }
 
-// Nonnegative gain truncated to its top 43 bits (relative resolution 2^-31),
-// then the inverted index: larger gain first, then smaller index.  Every
-// comparison of candidates goes by this key, inside a block as across blocks,
-// so the picks do not depend on how the columns are split over the blocks.
-// Indices are below 2^18, so every real candidate exceeds kNoCandidate.
+// The order of candidates.  A key holds the nonnegative gain truncated to its
+// top 43 bits (relative resolution 2^-31), then the inverted index: larger
+// gain first, then smaller index.  Candidates of one group (grp consecutive
+// columns) compare by their exact gains, then by index; as a group's columns
+// are consecutive, the order over all is: larger truncated gain, lower group,
+// larger exact gain, smaller index.  It does not depend on how the columns are
+// split over the blocks.  Indices are below 2^18, so every real candidate
+// exceeds kNoCandidate.
 __device__ __forceinline__ unsigned long long pack_key(double g, int idx) {
   const unsigned long long gb = (unsigned long long)__double_as_longlong(g) >> (kIndexBits + 1);
   return (gb << kIndexBits) | (kIndexMask - (unsigned long long)idx);
@@ -380,32 +389,84 @@ __device__ double block_max_all(double x, double* sd) {
   return s;
 }
 
-// The block's best unchosen column by key, published as its candidate for
-// the step.  With at most 64 columns wave 0 does it alone, one column per
-// lane, and no barrier follows: the callers' next step begins with one
-// (read_winner), and the gains and chosen flags it reads were last written by
-// wave 0 itself.
+// Of the lanes in `tie` (not empty), whose candidates' truncated gains are
+// equal, the one whose candidate (of a group, with a gain and an index) comes
+// first.  Every lane of the wave is active.
+__device__ __forceinline__ int first_of(unsigned long long tie, int group, long long g, int idx) {
+  if (__popcll(tie) > 1) {
+    bool in = (tie >> (threadIdx.x & 63)) & 1ull;
+    const int gm = wave_min_i32(in ? group : INT_MAX);
+    in = in && group == gm;
+    const unsigned long long top = wave_max_u64(in ? (unsigned long long)(g + 1) : 0ull);
+    in = in && (unsigned long long)(g + 1) == top;
+    const int im = wave_min_i32(in ? idx : INT_MAX);
+    tie = __ballot(in && idx == im);
+  }
+  return __builtin_ctzll(tie);
+}
+
+// The block's first unchosen column in the order of candidates, published as
+// its candidate for the step.  With at most 64 columns wave 0 does it alone,
+// one column per lane, and no barrier follows: the callers' next step begins
+// with one (read_winner), and the gains and chosen flags it reads were last
+// written by wave 0 itself.  More columns form one group with the others of
+// their block, so the exact gains decide.
 __device__ __forceinline__ unsigned long long column_key(const long long* sG, const unsigned char* ssel, int lo, int i,
                                                          int cnt, int S) {
   return i < cnt && !ssel[i] ? pack_key(fx_to_double(sG[i], S), lo + i) : kNoCandidate;
 }
-__device__ __forceinline__ void publish_argmax(const long long* sG, const unsigned char* ssel, int lo, int cnt,
-                                               int S, unsigned long long* slot, unsigned long long epoch,
+// The first of one wave's columns (one a lane): its lane and key (top: the
+// largest key, whose truncated gain others may share), and the best key of
+// the others.
+struct WaveBest {
+  unsigned long long key, second;
+  int lane;
+};
+__device__ __forceinline__ WaveBest wave_best(const IncDev& a, const long long* sG, unsigned long long mine, int lo) {
+  const int lane = threadIdx.x & 63;
+  WaveBest r;
+  r.key = wave_max_u64(mine);
+  r.lane = (int(kIndexMask - (r.key & kIndexMask)) - lo) & 63;
+  r.second = wave_max_u64(mine == r.key ? kNoCandidate : mine);
+  if (r.second > kNoCandidate && (r.second >> kIndexBits) == (r.key >> kIndexBits)) {
+    const unsigned long long tie = __ballot(mine > kNoCandidate && (mine >> kIndexBits) == (r.key >> kIndexBits));
+    r.lane = first_of(tie, group_of(a, lo + lane), (tie >> lane) & 1ull ? sG[lane] : 0, lo + lane);
+    r.key = lane_u64(mine, r.lane);
+    r.second = wave_max_u64(lane == r.lane ? kNoCandidate : mine);
+  }
+  return r;
+}
+__device__ __forceinline__ void publish_argmax(const IncDev& a, const long long* sG, const unsigned char* ssel, int lo,
+                                               int cnt, int S, unsigned long long* slot, unsigned long long epoch,
                                                unsigned long long* su) {
   if (cnt <= 64) {
     if (threadIdx.x >= 64) return;
-    const unsigned long long key = wave_max_u64(column_key(sG, ssel, lo, threadIdx.x, cnt, S));
-    if (threadIdx.x == 0) put(slot, key | epoch);
+    const WaveBest best = wave_best(a, sG, column_key(sG, ssel, lo, threadIdx.x, cnt, S), lo);
+    if (threadIdx.x == 0) put(slot, best.key | epoch);
     return;
   }
-  unsigned long long key = kNoCandidate;
-  for (int i = threadIdx.x; i < cnt; i += kBlock) key = max(key, column_key(sG, ssel, lo, i, cnt, S));
-  key = wave_max_u64(key);
-  if ((threadIdx.x & 63) == 0) su[threadIdx.x >> 6] = key;
+  __shared__ int si[kWaves];
+  long long g = -1;
+  int gi = INT_MAX;
+  for (int i = threadIdx.x; i < cnt; i += kBlock)
+    if (!ssel[i] && sG[i] > g) {   // increasing i: ties keep the smaller index
+      g = sG[i];
+      gi = lo + i;
+    }
+  unsigned long long top = wave_max_u64((unsigned long long)(g + 1));   // 0: no candidate
+  gi = wave_min_i32((unsigned long long)(g + 1) == top ? gi : INT_MAX);
+  if ((threadIdx.x & 63) == 0) {
+    su[threadIdx.x >> 6] = top;
+    si[threadIdx.x >> 6] = gi;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int q = 1; q < kWaves; ++q) key = max(key, su[q]);
-    put(slot, key | epoch);
+    for (int q = 1; q < kWaves; ++q)
+      if (su[q] > top || (su[q] == top && si[q] < gi)) {
+        top = su[q];
+        gi = si[q];
+      }
+    put(slot, (top ? pack_key(fx_to_double((long long)(top - 1), S), gi) : kNoCandidate) | epoch);
   }
   __syncthreads();
 }
@@ -438,27 +499,61 @@ __device__ int read_winner(const unsigned long long* slots, unsigned long long e
   return aborting ? -1 : int(kIndexMask - (m & kIndexMask));
 }
 
-// The two-word form of publish_argmax and read_winner, for kernels that predict
+// The form of publish_argmax and read_winner for kernels that predict
 // the next winner (at most 64 columns a block): the block's best key in word 0
-// of its slot and its second-best in word 1, each with the epoch bit.
-__device__ __forceinline__ void publish_rows(const long long* sG, const unsigned char* ssel, int lo, int cnt, int S,
-                                             unsigned long long* slot, unsigned long long epoch) {
+// of its slot, its second-best in word 1 and, where a group can reach over
+// several blocks (SPANS), the best one's exact gain in word 2, each with the
+// epoch bit.
+template <bool SPANS>
+__device__ __forceinline__ void publish_rows(const IncDev& a, const long long* sG, const unsigned char* ssel, int lo,
+                                             int cnt, int S, unsigned long long* slot, unsigned long long epoch) {
   if (threadIdx.x >= 64) return;
-  const unsigned long long mine = column_key(sG, ssel, lo, threadIdx.x, cnt, S);
-  const unsigned long long k1 = wave_max_u64(mine);
-  const unsigned long long k2 = wave_max_u64(mine == k1 ? kNoCandidate : mine);
-  if (threadIdx.x < 2) put(slot + threadIdx.x, (threadIdx.x ? k2 : k1) | epoch);
+  const WaveBest best = wave_best(a, sG, column_key(sG, ssel, lo, threadIdx.x, cnt, S), lo);
+  unsigned long long word = threadIdx.x ? best.second : best.key;
+  if (SPANS) {
+    // One store of three lanes; without a candidate the gain is not read.
+    const unsigned long long g = lane_u64((unsigned long long)sG[int(threadIdx.x) < cnt ? threadIdx.x : 0], best.lane);
+    if (threadIdx.x == 2) word = g & ~kEpoch;
+  }
+  if (threadIdx.x < (SPANS ? 3 : 2)) put(slot + threadIdx.x, word | epoch);
 }
 
-// read_winner for two-word slots: thread i < nb polls both words of block
-// i's slot and stores them (epoch bits cleared) in sk1 and sk2.  Returns the
-// winner's index, -1 when the launch is aborting.
-__device__ int read_winner_rows(const unsigned long long* slots, unsigned long long epoch, int nb, unsigned int* abort,
-                                unsigned int limit, unsigned long long* su, int* sflag, unsigned long long* sk1,
-                                unsigned long long* sk2) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+// Of the blocks' best candidates with the truncated gain of m (the one with
+// the smallest index, so the lowest group), the first one's index, the same in
+// every wave.
+__device__ __forceinline__ int first_of_blocks(const IncDev& a, unsigned long long m, int nb,
+                                            const unsigned long long* sk1, const unsigned long long* sk3) {
+  const int lane = threadIdx.x & 63;
+  const int gm = group_of(a, int(kIndexMask - (m & kIndexMask)));
   unsigned long long best = 0ull;
-  if (tid == 0) *sflag = 0;
+  int bi = INT_MAX;
+#pragma unroll 1
+  for (int b = lane; b < nb; b += 64) {             // increasing b: ties keep the smaller index
+    const int i = int(kIndexMask - (sk1[b] & kIndexMask));
+    if (sk1[b] > kNoCandidate && (sk1[b] >> kIndexBits) == (m >> kIndexBits) && group_of(a, i) == gm && sk3[b] + 1 > best) {
+      best = sk3[b] + 1;
+      bi = i;
+    }
+  }
+  const unsigned long long top = wave_max_u64(best);
+  return wave_min_i32(best == top ? bi : INT_MAX);
+}
+
+// read_winner for such slots: thread i < nb polls words 0 and 1 of block i's
+// slot and stores them (epoch bits cleared) in sk1 and sk2.  Returns the
+// winner's index, -1 when the launch is aborting.  With SPANS the blocks whose
+// truncated gain is the winner's are told apart by word 2 (sk3), read only
+// then; sflag has a second word for that.
+template <bool SPANS>
+__device__ int read_winner_rows(const IncDev& a, const unsigned long long* slots, unsigned long long epoch, int nb,
+                                unsigned long long* su, int* sflag, unsigned long long* sk1, unsigned long long* sk2,
+                                unsigned long long* sk3) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  unsigned long long own = 0ull;
+  if (tid == 0) {
+    sflag[0] = 0;
+    if (SPANS) sflag[1] = 0;
+  }
   __syncthreads();
   if (tid < nb) {
     const unsigned long long* p = slots + size_t(tid) * kSlotStride;
@@ -466,28 +561,43 @@ __device__ int read_winner_rows(const unsigned long long* slots, unsigned long l
     for (unsigned int spins = 0; !done; ++spins) {
       const unsigned long long x0 = get(p), x1 = get(p + 1);
       if ((x0 & kEpoch) == epoch && (x1 & kEpoch) == epoch) {
-        best = x0 & ~kEpoch;
-        sk1[tid] = best;
+        own = x0 & ~kEpoch;
+        sk1[tid] = own;
         sk2[tid] = x1 & ~kEpoch;
         done = true;
       } else {
-        if (give_up(spins, limit, abort)) {
-          *sflag = 1;
+        if (give_up(spins, a.poll_limit, a.abort)) {
+          sflag[0] = 1;
           break;
         }
         __builtin_amdgcn_s_sleep(1);
       }
     }
   }
-  best = wave_max_u64(best);
+  const unsigned long long best = wave_max_u64(own);
   if (lane == 0) su[w] = best;
   __syncthreads();
   unsigned long long m = su[0];
 #pragma unroll
   for (int q = 1; q < kWaves; ++q) m = su[q] > m ? su[q] : m;
-  const bool aborting = *sflag != 0;
+  const bool tied = own > kNoCandidate && (own >> kIndexBits) == (m >> kIndexBits);
+  if (SPANS && tied && own != m) sflag[1] = 1;
+  const bool aborting = sflag[0] != 0;
   __syncthreads();
-  return aborting ? -1 : int(kIndexMask - (m & kIndexMask));
+  if (aborting) return -1;
+  if (SPANS && sflag[1]) {
+    if (tied) {
+      unsigned long long x = 0ull;
+      if (!wait_slot(slots + size_t(tid) * kSlotStride + 2, a.abort, a.poll_limit,
+                     [epoch](unsigned long long v) { return (v & kEpoch) == epoch; }, x))
+        sflag[0] = 1;
+      sk3[tid] = x & ~kEpoch;
+    }
+    __syncthreads();
+    if (sflag[0]) return -1;
+    return first_of_blocks(a, m, nb, sk1, sk3);
+  }
+  return int(kIndexMask - (m & kIndexMask));
 }
 
 }  // namespace

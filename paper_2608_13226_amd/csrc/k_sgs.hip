@@ -359,7 +359,8 @@ __global__ __launch_bounds__(BT) void sgs_dense_kernel(SgsDev a) {
       int t = -1;
       if (ok) {
         const unsigned long long kk = __hip_atomic_load(a.key + step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        t = int(kIndexMask - (kk & kIndexMask));
+        // No strip has a winner when every gain is a NaN: the key is then none.
+        t = min(int(kIndexMask - (kk & kIndexMask)), a.n - 1);
         const int ts = t / kStrip;
         if (int(blockIdx.x) == ts % int(gridDim.x)) put(a.mask + t, 1u);   // owner of item (0, ts)
         if (blockIdx.x == 0) {

@@ -179,11 +179,15 @@ cp_status coverprune_fst_capacity(const void* feats, cp_dtype dtype, int64_t n, 
  *   flags     CP_SGS_DENSE: every step sums every candidate's gain over the
  *             whole matrix (K full reads of the cost), in float64.  Up to
  *             n = 8192, with the workspace of coverprune_sgs_workspace, the
- *             picks come from the incremental form instead when a check on
- *             the device finds every cost >= 0 and every capacity finite,
- *             >= 0 and, if positive, of at least 36 bits on that form's grid;
- *             otherwise, or with a workspace for the sweeps alone, the whole
- *             matrix is read each step.
+ *             result of the incremental form's launch stands instead when
+ *             the device finds every cost >= 0, every capacity finite and
+ *             >= 0, the last gain at least n 2^30 and the last objective (if
+ *             asked for) n 2^36 units of that form's grid, which bounds the
+ *             error of its sums to 2^-30 and 2^-36, and no gains that only
+ *             differ below 2^-31 met in a comparison.  Otherwise, for k = n,
+ *             for a few picks of a small scene (k <= 12, n <= 2048), or with
+ *             a workspace for the sweeps alone, the whole matrix is read
+ *             each step.
  *             CP_SGS_INCREMENTAL: the gains are summed once at b = c0 and then
  *             updated, step by step, from the rows of the targets whose best
  *             cost the pick lowers (their old and new b); the terms are the

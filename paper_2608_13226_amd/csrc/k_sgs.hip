@@ -36,12 +36,20 @@
 // of few targets after the first steps.  Up to kFastN tokens the call
 // therefore runs the incremental greedy (the rows schedule of k_sgs_inc.hip):
 // the same float32 differences and exact products, summed in 64-bit fixed
-// point on a grid of 2^-62 of the total instead of in float64, so gains differ
-// by far less than the differences' own rounding (2^-24).  It serves costs in
-// [0, inf] and capacities in [0, inf) whose smallest positive one is not below
-// 2^-26 of the grid's range (kUnfitBits); its first pass checks that, and
-// the sweeps run only when it raised `unfit`.  n = 4096, K = 410: 10.8 ms of
-// sweeps (26 us a step, 2.6 TB/s from the Infinity Cache).
+// point on a grid of 2^-62 of the total instead of in float64.  Its result
+// stands when it is the sweeps' up to the differences' own rounding (2^-24):
+//  - costs in [0, inf] and capacities in [0, inf), checked by its first pass;
+//  - every gain it compared lies far above the grid.  A sum falls short of the
+//    exact one by less than n units, and the gains of the picks fall, so the
+//    last one tells (kGainBits: it is within 2^-30), and the last objective
+//    likewise (kObjBits: 2^-36).  A c0 far above the costs, capacities of many
+//    magnitudes or targets all covered fail here.  Scenes of the usual kind
+//    end 2^3 to 2^9 above it (10 % of 4096 tokens: 2^46.7 against 2^42, 90 % of
+//    2048: 2^43.5 against 2^41);
+//  - no exact gain had to decide between candidates of equal key (about 2^-31;
+//    the sweeps tell apart a bit more of them).
+// Otherwise the sweeps run after it and write every output again.  n = 4096,
+// K = 410: 10.8 ms of sweeps (26 us a step, 2.6 TB/s from the Infinity Cache).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -81,7 +89,10 @@ struct SgsDev {
   unsigned int* abort;       // set when the step wait gives up
   unsigned int poll_limit;   // polls before it gives up (WaitPolicy)
   unsigned int abort_init;   // the abort flag's value at launch
-  const unsigned int* gate;  // the launch runs only when this word is set (null: always)
+  unsigned int* gate;        // the launches run only when this word is set (null: always)
+  SgsChecked inc;            // with gate (inc.unfit): what the incremental greedy noted,
+  const double* last_gain;   // the gain of its last pick
+  const double* last_obj;    // and its last objective (null: not asked for)
   int P, S, rows;            // panels, strips, rows per panel
 };
 
@@ -154,11 +165,29 @@ __device__ double block_sum(double x, double* sd) {
   return s;
 }
 
+// Bits of a last gain and objective on the grid, beyond those of n.
+constexpr int kGainBits = 30;
+constexpr int kObjBits = 36;
+
+// Whether the incremental greedy's result does not stand.  One that gave up
+// does: its picks are marked.
+__device__ __forceinline__ bool sweeps_needed(const SgsDev& a) {
+  if (get(a.gate)) return true;
+  if (*a.inc.abort) return false;
+  const double unit = __builtin_ldexp(double(a.n), -*a.inc.scale);   // n units of the grid
+  return *a.inc.tie || !(*a.last_gain >= __builtin_ldexp(unit, kGainBits)) ||
+         (a.last_obj && !(*a.last_obj >= __builtin_ldexp(unit, kObjBits)));
+}
+
 __global__ void sgs_init_kernel(SgsDev a) {
   const int gt = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
-  if (a.gate && !*a.gate) {
-    if (gt == 0) *a.abort = 0u;
-    return;
+  if (a.gate) {
+    const bool run = sweeps_needed(a);
+    if (gt == 0) {
+      if (run) put(a.gate, 1u);   // another block that reads it now finds the same
+      *a.abort = 0u;
+    }
+    if (!run) return;
   }
   for (int j = gt; j < a.n; j += nt) {
     a.mask[j] = 0u;
@@ -430,12 +459,19 @@ size_t sgs_workspace_bytes(int64_t n, int64_t k) {
 }
 
 hipError_t launch_sgs_dense(const SgsParams& p, hipStream_t stream) {
-  const unsigned int* gate = nullptr;
-  if (p.n <= kFastN && p.c0 > 0.f && p.workspace_bytes >= sgs_workspace_bytes(p.n, p.k)) {
+  // With every token picked the objective is only what tokens cost themselves,
+  // mostly nothing, and the sweeps would have to follow.
+  SgsChecked checked{};
+  const double* last_gain = nullptr;
+  if (p.n <= kFastN && p.k < p.n && p.c0 > 0.f && p.workspace_bytes >= sgs_workspace_bytes(p.n, p.k)) {
+    const Layout L = layout(p.n, p.k);
     SgsParams q = p;
-    q.workspace = static_cast<char*>(p.workspace) + layout(p.n, p.k).total;
-    q.workspace_bytes = p.workspace_bytes - layout(p.n, p.k).total;
-    const hipError_t e = launch_sgs_checked(q, &gate, stream);
+    q.workspace = static_cast<char*>(p.workspace) + L.total;
+    q.workspace_bytes = p.workspace_bytes - L.total;
+    // Gains that the caller does not want go where the sweeps' partial ones would.
+    if (!q.step_gain) q.step_gain = reinterpret_cast<double*>(static_cast<char*>(p.workspace) + L.partial);
+    last_gain = q.step_gain + (p.k - 1);
+    const hipError_t e = launch_sgs_checked(q, &checked, stream);
     if (e != hipSuccess) return e;
   }
   const bool vec4 = (p.n % 4) == 0;
@@ -475,7 +511,10 @@ hipError_t launch_sgs_dense(const SgsParams& p, hipStream_t stream) {
   const WaitPolicy wp = wait_policy();
   a.poll_limit = wp.limit;
   a.abort_init = wp.preset;
-  a.gate = gate;
+  a.gate = checked.unfit;
+  a.inc = checked;
+  a.last_gain = last_gain;
+  a.last_obj = p.step_objective ? p.step_objective + (p.k - 1) : nullptr;
   a.P = P;
   a.S = S;
   a.rows = rows;

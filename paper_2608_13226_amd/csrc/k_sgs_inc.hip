@@ -1739,7 +1739,10 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
         if (__popcll(tie) > 1) {
           const unsigned lm = half_max_u32(unsigned(u >> kKeyLow) == hm ? unsigned(u) & kKeyLowMask : 0u);
           tie &= __ballot((unsigned(u) & kKeyLowMask) == lm);
-          if (__popcll(tie) > 1) tie = 1ull << first_of(tie, mygrp, gl, myidx);
+          if (__popcll(tie) > 1) {
+            if (((tie >> lane) & 1ull) && gl != lane_i64(gl, __builtin_ctzll(tie))) note_tie(a);
+            tie = 1ull << first_of(tie, mygrp, gl, myidx);
+          }
         }
         const int slot = __builtin_ctzll(tie);
         const long long g = lane_i64(gl, slot);
@@ -1848,6 +1851,15 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
       const int wb = wave_min_i32((unsigned long long)(gx + 1) == gt ? bx : INT_MAX);
       const int t = min(wb * a.W + int(sgi[wb] & 0xffu), a.n - 1);
       const long long gb = word_gain(sgw[0][wb]);
+      if (w == 0 && (a.abort_init & 2u)) {
+#pragma unroll
+        for (int r = 0; r <= kPub; ++r)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const long long gq = word_gain(sgw[r][lane + 64 * q]);
+            if (gq != gb && gain_key(gq) == top) note_tie(a);
+          }
+      }
       const int len = __builtin_amdgcn_readfirstlane(int(sgl[wb]) & 0xfff);
       const bool listed = len <= a.lcap;
       lds_barrier();                                                // every wave has read the best costs
@@ -1907,10 +1919,6 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
 template <int NG>
 __global__ __launch_bounds__(kListBlock) void sgs_list_kernel(IncDev a) { list_body<NG>(a, blockIdx.x, gridDim.x); }
 
-// The dense form's guard (k_sgs.hip): a term below its target's largest one
-// by 2^-12 still has the 24 bits of the float32 difference in it.
-constexpr int kUnfitBits = 36;
-
 // The fixed-point scale of a scene (one block; the sum in the same order as
 // every block of the greedy would take it).
 __global__ __launch_bounds__(kBlock) void inc_scale_kernel(IncDev a, int* scale) {
@@ -1918,14 +1926,9 @@ __global__ __launch_bounds__(kBlock) void inc_scale_kernel(IncDev a, int* scale)
   const int S = fixed_scale(a, sd);
   if (threadIdx.x == 0) *scale = S;
   if (a.abort_init & 2u) {
-    // Capacities the fixed point does not hold: negative, infinite, NaN, or a
-    // positive one whose largest term keeps fewer than kUnfitBits bits.
+    // Capacities the fixed point does not hold: negative, infinite or NaN.
     bool bad = false;
-    for (int j = threadIdx.x; j < a.n; j += kBlock) {
-      const float v = a.v[j];
-      bad = bad || !(v >= 0.f && v < __builtin_inff()) ||
-            (v > 0.f && __builtin_ldexp(double(v) * double(a.c0), S) < double(1ull << kUnfitBits));
-    }
+    for (int j = threadIdx.x; j < a.n; j += kBlock) bad = bad || !(a.v[j] >= 0.f && a.v[j] < __builtin_inff());
     if (bad) atomicOr(a.abort + kUnfitWord, 1u);
   }
 }
@@ -2072,17 +2075,20 @@ bool use_rows(int64_t n, int W) { return n <= kRowsMaxN && W <= kRowsMaxW; }
 // launch whatever the schedule asked for: the rows form spends some 0.1 ms on
 // its launches and first steps before its steps get cheaper than the exchange
 // form's 5 to 7 us (k = 12 of 256 tokens: 115 against 160 us, 30 of 300: 210
-// against 185, 51 of 1024: 390 against 292).  Same result.
+// against 185, 51 of 1024: 390 against 292).  Same result.  With the data
+// checked for the dense form the sweeps are the alternative, and as fast up
+// to kCheckedShortK picks (10 of 1024: 153 us of sweeps, 178 of the rows
+// form; 12 of 256: 139, 144; 12 of 2048: 268, 265; 16 of 2048: 329, 297).
 // Blocks of a scene's greedy, and whether it is the rows form.  The rows form
 // takes one block per kRowsPer tokens (up to one per compute unit: the early
 // steps and the hits' row segments spread over more of the chip, 4096 tokens
 // 0.05 ms faster than with one per 32), the exchange form one per 64.
 constexpr int kRowsPer = 16;
-constexpr int kShortN = 2048, kShortK = 20;
-bool short_greedy(int64_t n, int64_t k) { return n <= kShortN && k <= kShortK; }
-int inc_blocks(int64_t n, int64_t k, int cus, bool compact, bool* rows) {
+constexpr int kShortN = 2048, kShortK = 20, kCheckedShortK = 12;
+bool short_greedy(int64_t n, int64_t k, int64_t short_k = kShortK) { return n <= kShortN && k <= short_k; }
+int inc_blocks(int64_t n, int64_t k, int cus, bool compact, bool* rows, int64_t short_k = kShortK) {
   const int nb = blocks_for(n, cus, kRowsPer);
-  *rows = !compact && !short_greedy(n, k) && use_rows(n, cols_for(n, nb));
+  *rows = !compact && !short_greedy(n, k, short_k) && use_rows(n, cols_for(n, nb));
   return *rows ? nb : blocks_for(n, cus, 64);
 }
 
@@ -2102,11 +2108,13 @@ const void* rows_batch_kernel(int64_t n, int W) {
 }
 
 // The step from which a scene's lists serve, and whether they do (there have
-// to be some steps left to pay for building them).  A step of the rows kernel
-// takes 7 us, one of the list kernel 1.5; but lists built too early are long
+// to be some steps left to pay for building them: two launches of some 50 us).
+// A step of the rows kernel takes 7 us, one of the list kernel 1.5; but lists built too early are long
 // (n / 320: four scenes of 6272 tokens 4.0 ms instead of 2.6; n / 192: level).
+// 12 steps: 20 picks of 1024 tokens 302 us with lists and 242 without, 28 of
+// 2500 641 and 590, 61 of 6272 1283 and 1247.
 int list_step(int64_t n) { return int(std::max<int64_t>(8, std::min<int64_t>(128, n / 128))); }
-bool lists_for(int64_t n, int64_t k, int W) { return n <= kListMaxN && W <= kRowsMaxW && k > list_step(n) + 8; }
+bool lists_for(int64_t n, int64_t k, int W) { return n <= kListMaxN && W <= kRowsMaxW && k > list_step(n) + 12; }
 
 // Exchange slots and lists, the first pass's partial gains and scale, then
 // (when the rows form may run) T.
@@ -2251,13 +2259,15 @@ const void* list_kernel(int W) {
 // fst_epilogue_sgs_kernel (and the scale before it), so the first pass is
 // skipped and the gains come from its partial sums.
 hipError_t run_incremental(const SgsParams& p, bool compact, const SgsFused* fused, hipStream_t stream,
-                           const unsigned int** unfit = nullptr) {
+                           SgsChecked* checked = nullptr) {
   int cus = 0;
   hipError_t e = hipError_t(device_cus(&cus));
   if (e != hipSuccess) return e;
   bool rows = false;
-  const int nb = inc_blocks(p.n, p.k, cus, compact, &rows);
+  const int nb = inc_blocks(p.n, p.k, cus, compact, &rows, checked ? kCheckedShortK : kShortK);
   const int W = cols_for(p.n, nb);
+  // note_tie covers the exchange of the rows form with one column group.
+  if (checked && (!rows || W > 64)) return hipSuccess;
   const void* kernel = rows ? rows_kernel(p.n, W) : reinterpret_cast<const void*>(sgs_inc_kernel);
   const size_t lds = rows ? lds_rows(W, p.n) : lds_for(W);
   if ((e = fits(kernel, lds)) != hipSuccess) return e;
@@ -2267,9 +2277,12 @@ hipError_t run_incremental(const SgsParams& p, bool compact, const SgsFused* fus
     a.part = fused->part;
     a.P = fused->P;
   }
-  if (unfit) {
+  if (checked) {
     a.abort_init |= 2u;
-    *unfit = a.abort + kUnfitWord;
+    checked->unfit = a.abort + kUnfitWord;
+    checked->tie = a.abort + kTieWord;
+    checked->abort = a.abort;
+    checked->scale = a.scale;
   }
   // The early kernel runs the first steps, while they improve many targets,
   // the rows kernel those up to the list phase (or the end), the list kernel
@@ -2306,8 +2319,9 @@ hipError_t launch_sgs_incremental(const SgsParams& p, bool compact, hipStream_t 
   return run_incremental(p, compact, nullptr, stream);
 }
 
-hipError_t launch_sgs_checked(const SgsParams& p, const unsigned int** unfit, hipStream_t stream) {
-  return run_incremental(p, false, nullptr, stream, unfit);
+hipError_t launch_sgs_checked(const SgsParams& p, SgsChecked* checked, hipStream_t stream) {
+  *checked = SgsChecked{};
+  return run_incremental(p, false, nullptr, stream, checked);
 }
 
 // coverprune_prune: the rows schedule's workspace, then the epilogue's

@@ -73,10 +73,18 @@ hipError_t launch_sgs_dense(const SgsParams& p, hipStream_t stream);
 // schedule (about 16 bytes per token).
 size_t sgs_inc_workspace_bytes(int64_t n, int64_t k, bool compact);
 hipError_t launch_sgs_incremental(const SgsParams& p, bool compact, hipStream_t stream);
-// The rows schedule with its data checked on the device: *unfit (a word of
-// the workspace) is set when they are outside the fixed point's domain, and
-// the outputs are then to be computed by another launch.
-hipError_t launch_sgs_checked(const SgsParams& p, const unsigned int** unfit, hipStream_t stream);
+// The rows schedule with its data checked on the device; `unfit` stays null
+// where it does not serve the scene.  Otherwise words of the workspace: *unfit
+// is set when the data are outside the fixed point's domain (the outputs are
+// then not written), *tie when an exact gain decided between candidates,
+// *abort when the launch gave up; *scale is the grid, 2^-scale.
+struct SgsChecked {
+  unsigned int* unfit;
+  const unsigned int* tie;
+  const unsigned int* abort;
+  const int* scale;
+};
+hipError_t launch_sgs_checked(const SgsParams& p, SgsChecked* checked, hipStream_t stream);
 // The incremental greedy after launch_fst_epilogue_sgs (coverprune_prune):
 // the rows schedule, whose T and step-0 partial gains that epilogue writes.
 // sgs_fused_fits: n a multiple of 64 that the rows schedule serves on this

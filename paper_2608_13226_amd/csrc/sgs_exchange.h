@@ -94,6 +94,13 @@ struct IncDev {
 constexpr int kUnfitWord = 16;
 __device__ __forceinline__ bool unfit(const IncDev& a) { return (a.abort_init & 2u) && a.abort[kUnfitWord]; }
 
+// Also with the data checked: word kTieWord is set when an exact gain, not
+// its key, had to decide between candidates (the kernels in flight go on).
+constexpr int kTieWord = 17;
+__device__ __forceinline__ void note_tie(const IncDev& a) {
+  if (a.abort_init & 2u) atomicOr(a.abort + kTieWord, 1u);
+}
+
 // The block that owns column c: c / W as the high word of c times
 // floor(2^32 / W) + 1, exact for c < 2^18 and 2 <= W <= 2^13 (the product
 // exceeds 2^32 c / W by less than c, which moves c / W by less than 2^-14,
@@ -182,7 +189,7 @@ __global__ void sgs_inc_init_kernel(IncDev a) {
   for (int j = gt; j < a.n; j += nt)
     if (a.assign) a.assign[j] = -1;
   if (gt == 0) *a.abort = a.abort_init & 1u;
-  if (gt == 0) a.abort[kUnfitWord] = 0u;
+  if (gt == 0) a.abort[kUnfitWord] = a.abort[kTieWord] = 0u;
 }
 
 // Wave reductions without LDS traffic: DPP moves within each row of 16
@@ -430,7 +437,9 @@ __device__ __forceinline__ WaveBest wave_best(const IncDev& a, const long long* 
   r.second = wave_max_u64(mine == r.key ? kNoCandidate : mine);
   if (r.second > kNoCandidate && (r.second >> kIndexBits) == (r.key >> kIndexBits)) {
     const unsigned long long tie = __ballot(mine > kNoCandidate && (mine >> kIndexBits) == (r.key >> kIndexBits));
-    r.lane = first_of(tie, group_of(a, lo + lane), (tie >> lane) & 1ull ? sG[lane] : 0, lo + lane);
+    const long long g = (tie >> lane) & 1ull ? sG[lane] : 0;
+    r.lane = first_of(tie, group_of(a, lo + lane), g, lo + lane);
+    if (((tie >> lane) & 1ull) && g != sG[r.lane]) note_tie(a);
     r.key = lane_u64(mine, r.lane);
     r.second = wave_max_u64(lane == r.lane ? kNoCandidate : mine);
   }
@@ -595,6 +604,7 @@ __device__ int read_winner_rows(const IncDev& a, const unsigned long long* slots
     }
     __syncthreads();
     if (sflag[0]) return -1;
+    if (tied && sk3[tid] != sk3[block_of(a, int(kIndexMask - (m & kIndexMask)))]) note_tie(a);
     return first_of_blocks(a, m, nb, sk1, sk3);
   }
   return int(kIndexMask - (m & kIndexMask));

@@ -149,7 +149,9 @@ cp_status coverprune_fst_cost(const void* feats, cp_dtype dtype, int64_t n, int6
  *   alpha     term weights, finite and >= 0 (the experiments use 1, Sec. 5.1)
  *   capacity  [n] float output v, the input of the greedy and of Lite
  *   score     [n] double output r (may be NULL)
- *   workspace about (20 + 28 n_nb) bytes per token
+ *   workspace about (28 + 28 n_nb) bytes per token; 16 fewer, without the
+ *             tables' spatial order (12 + 28 n_nb and the rounding of each
+ *             array to 256 bytes), also do, more slowly
  */
 typedef struct {
   float alpha_f, alpha_x, alpha_tau;
@@ -432,7 +434,8 @@ cp_status coverprune_sgs_local_select(const float* cost, int64_t n, const float*
  *   objective      [1] double output (may be NULL): <P, C_S> of the final plan
  * With `follow` set and both step outputs NULL only the final plan is solved.
  * Workspace: about 8 k + 40 bytes per token plus 8 k per 64 tokens; for
- * n <= 2048 and k <= 256 at least n^2 bytes plus 260 KB.
+ * n <= 2048 and k <= 256 at least n^2 bytes plus 260 KB, below which the
+ * separate launches run.
  */
 #define CP_SGS_LITERAL_MAX_K 4096
 #define CP_SGS_LITERAL_MAX_ROUNDS 1000000

@@ -38,6 +38,8 @@ CP_F32, CP_BF16 = 0, 1
 CP_SGS_DENSE = 0
 CP_SGS_INCREMENTAL = 1
 CP_SGS_COMPACT = 2
+# Up to here the dense form's workspace holds the incremental form's as well.
+DENSE_INCREMENTAL_N = 8192
 
 
 class CoverPruneError(RuntimeError):
@@ -327,7 +329,13 @@ def sgs_select(cost: torch.Tensor, capacity: torch.Tensor, k: int, c0: Optional[
     flags = (CP_SGS_INCREMENTAL | (CP_SGS_COMPACT if compact else 0)) if incremental else CP_SGS_DENSE
     need = lib.coverprune_sgs_workspace(n, int(k), flags)
     if workspace is None:
-        workspace = _workspace(need, dev)
+        try:
+            workspace = _workspace(need, dev)
+        except torch.cuda.OutOfMemoryError:
+            # The dense form also runs in its sweeps' part, a few MB.
+            if flags != CP_SGS_DENSE or n > DENSE_INCREMENTAL_N:
+                raise
+            workspace = _workspace(need - lib.coverprune_sgs_workspace(n, int(k), CP_SGS_INCREMENTAL), dev)
     _check(lib.coverprune_sgs_select(_ptr(cost), n, _ptr(capacity), int(k), float(c0), flags,
                                      _ptr(sel), _ptr(gain), _ptr(obj), _ptr(assign), _ptr(workspace),
                                      workspace.numel(), _stream(stream)))

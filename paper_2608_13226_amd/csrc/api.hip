@@ -451,7 +451,8 @@ cp_status coverprune_sgs_literal_select(const float* cost, int64_t n, const floa
     return fail(CP_ERR_INVALID_ARG, "rounds = %d outside [1, %d]", (int)rounds, CP_SGS_LITERAL_MAX_ROUNDS);
   if (!cost || !capacity || !selected) return fail(CP_ERR_INVALID_ARG, "cost, capacity and selected must be non-NULL");
   if (!aligned16(cost)) return fail(CP_ERR_INVALID_ARG, "cost is not 16-byte aligned");
-  cp_status st = check_workspace(workspace, workspace_bytes, coverprune_sgs_literal_workspace(n, k));
+  // The separate launches run in a workspace of their own size.
+  cp_status st = check_workspace(workspace, workspace_bytes, cp::sgs_literal_min_workspace_bytes(n, k));
   if (st != CP_OK) return st;
 
   cp::LiteralParams p;
@@ -501,7 +502,8 @@ cp_status coverprune_fst_capacity(const void* feats, cp_dtype dtype, int64_t n, 
   const float a[3] = {alpha.alpha_f, alpha.alpha_x, alpha.alpha_tau};
   for (float x : a)
     if (!std::isfinite(x) || x < 0.f) return fail(CP_ERR_INVALID_ARG, "capacity weights must be finite and >= 0");
-  if ((st = check_workspace(workspace, workspace_bytes, coverprune_fst_capacity_workspace(n, n_nb))) != CP_OK)
+  // It also runs without the scratch space of the spatial order.
+  if ((st = check_workspace(workspace, workspace_bytes, cp::capacity_min_workspace_bytes(n, n_nb))) != CP_OK)
     return st;
 
   cp::CapacityParams p;

@@ -263,6 +263,7 @@ constexpr int kCapSortN = 1024;
 }  // namespace
 
 size_t capacity_workspace_bytes(int64_t n, int64_t nn) { return cap_layout(n, nn).total; }
+size_t capacity_min_workspace_bytes(int64_t n, int64_t nn) { return cap_layout(n, nn).spos; }
 
 hipError_t launch_capacity(const CapacityParams& c, hipStream_t stream) {
   const CapLayout L = cap_layout(c.n, c.nn);
@@ -289,7 +290,7 @@ hipError_t launch_capacity(const CapacityParams& c, hipStream_t stream) {
   cap_init_kernel<<<1, 64, 0, stream>>>(p.maxbits);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   int32_t* table = reinterpret_cast<int32_t*>(w + L.table);
-  if (c.n >= kCapSortN) {
+  if (c.n >= kCapSortN && c.workspace_bytes >= L.total) {
     float4* spos = reinterpret_cast<float4*>(w + L.spos);
     p.spos = spos;
     e = launch_knn_sorted(c.pos, c.n, p.g, table, spos, w + L.boxes, stream);

@@ -794,6 +794,8 @@ hipError_t try_persistent(const LiteralParams& q, hipStream_t stream, bool* done
 
 }  // namespace
 
+size_t sgs_literal_min_workspace_bytes(int64_t n, int64_t k) { return lit_layout(n, k).total; }
+
 size_t sgs_literal_workspace_bytes(int64_t n, int64_t k) {
   return std::max(lit_layout(n, k).total, lit_pers_serves(n, k) ? lit_pers_bytes(n) : size_t(0));
 }

@@ -145,6 +145,8 @@ struct LiteralParams {
   size_t workspace_bytes;
 };
 
+// sgs_literal_min_workspace_bytes: what the separate launches need.
+size_t sgs_literal_min_workspace_bytes(int64_t n, int64_t k);
 size_t sgs_literal_workspace_bytes(int64_t n, int64_t k);
 hipError_t launch_sgs_literal(const LiteralParams& p, hipStream_t stream);
 
@@ -164,7 +166,9 @@ struct CapacityParams {
   size_t workspace_bytes;
 };
 
+// With capacity_min_workspace_bytes the tokens stay in index order.
 size_t capacity_workspace_bytes(int64_t n, int64_t nn);
+size_t capacity_min_workspace_bytes(int64_t n, int64_t nn);
 hipError_t launch_capacity(const CapacityParams& p, hipStream_t stream);
 
 // CoverPrune-Lite.

@@ -563,7 +563,9 @@ __global__ __launch_bounds__(kBlock) void lit_persistent_kernel(LitPers p) {
       double s = 0.0;
 #pragma unroll
       for (int q = 0; q < kWaves; ++q) s += sred[q][lane & 7];
-      const unsigned long long key = ok ? ~f64_order(s) : 0ull;
+      // As in lit_select_kernel a NaN (an infinite cost where nothing is left)
+      // comes after every finite score, whatever its sign.
+      const unsigned long long key = ok ? ~f64_order(s < DBL_MAX ? s : double(__builtin_inff())) : 0ull;
       const unsigned long long top = wave_max_u64(key);
       const int bi = wave_min_i32(ok && key == top ? col : INT_MAX);
       // The best one's score (none: no word of it is taken).

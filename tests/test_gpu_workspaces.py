@@ -44,7 +44,7 @@ def _literal_bytes(n, k):
     return (up(n * kp * 8) + up(kp * 8) + 2 * up(n * 8) + up(nrb * kp * 8) + up(panels * n * 8) + up(nrb * 8) + up(n))
 
 
-@pytest.mark.parametrize("kind", ["plain", "underflow", "no capacity"])
+@pytest.mark.parametrize("kind", ["plain", "underflow", "unreachable", "no capacity"])
 @pytest.mark.parametrize("n,k", [(65, 9), (777, 40), (2048, 70)])
 def test_literal_as_separate_launches(n, k, kind):
     import paper_2608_13226_amd as cp
@@ -54,6 +54,10 @@ def test_literal_as_separate_launches(n, k, kind):
     eps = 0.05
     if kind == "underflow":
         eps = 1e-3                                  # E is 0 beyond C = 0.75
+    elif kind == "unreachable":
+        # A fifth of the tokens do not reach some targets: scores of infinity
+        # or, with no residual there, NaN, which come after all others.
+        c[(rng.random(n) < 0.2)[:, None] & (rng.random((n, n)) < 0.2)] = np.inf
     np.fill_diagonal(c, 0.0)
     v = rng.random(n).astype(np.float32)
     if kind == "no capacity":

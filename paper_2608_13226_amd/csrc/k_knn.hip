@@ -323,7 +323,7 @@ __device__ __forceinline__ int cell_of(float x, float y, float z, const float* l
   const float p[3] = {x, y, z};
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const int c = min(max(int((p[a] - lo[a]) * scale), 0), 31);   // NaN converts to 0
+    const int c = int(fminf(fmaxf((p[a] - lo[a]) * scale, 0.f), 31.f));   // fmaxf takes a NaN to 0
 #pragma unroll
     for (int b = 0; b < 5; ++b) code |= ((c >> b) & 1) << (3 * b + a);
   }

@@ -90,7 +90,8 @@ hipError_t launch_step_floor(const float* rows, int n_rows, int row_len, int rou
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-  // The greedy's grid for a scene of n_rows tokens.
+  // One block per 64 rows: the greedy's grid for n_rows = 16384, its exchange
+  // form's for any.
   const int nb = blocks_for(n_rows, cus, 64);
   ProbeDev a{};
   a.rows = rows;

@@ -1543,7 +1543,7 @@ __device__ __forceinline__ void list_body(const IncDev& a, int blk, int nb) {
     {
       const unsigned long long ep = epoch_of(xc);
       const unsigned long long* slots = cand_slot(a.cand, xc & 1, 0) + kListWord;
-      constexpr int kRead = kMaxBlocks / (8 * kListWaves);          // loads in flight: 8
+      constexpr int kRead = kMaxBlocks / (8 * kListWaves);          // loads in flight: 4
       const int r = lane & 7;
       unsigned long long x[kRead];
       bool need[kRead];
@@ -2118,7 +2118,7 @@ bool lists_for(int64_t n, int64_t k, int W) { return n <= kListMaxN && W <= kRow
 
 // Exchange slots and lists, the first pass's partial gains and scale, then
 // (when the rows form may run) T.
-constexpr int kPassParts = 3;   // row ranges of the first pass (three blocks per compute unit fit at once)
+constexpr int kPassParts = 3;   // row ranges of the first pass: 768 blocks at 16384 tokens, 192 at 4096
 constexpr int kListOwnK = 128;  // up to this many picks the lists take the place of the rows of T
 struct IncLayout {
   size_t part, scale, T, epart, epart_bytes, lists, ho_gain, ho_sel, ho_b, misc, total;
@@ -2146,7 +2146,7 @@ IncLayout inc_layout(int64_t n, int64_t k, bool compact) {
     L.ho_gain = o; o += a256(size_t(n) * 8);
     L.ho_sel = o;  o += a256(size_t(n));
     L.ho_b = o;    o += a256(size_t(rows_ldt(n)) * 4);
-    L.misc = o;    o += a256(24 + 4 + size_t(kMaxBlocks) * 4);   // objective, (unused), next step
+    L.misc = o;    o += a256(24 + 4 + size_t(kMaxBlocks) * 4);   // objective, exchanges, next step; the rest is spare
   }
   L.total = o;
   return L;

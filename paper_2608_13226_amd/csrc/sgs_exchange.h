@@ -104,8 +104,8 @@ __device__ __forceinline__ void note_tie(const IncDev& a) {
 // The block that owns column c: c / W as the high word of c times
 // floor(2^32 / W) + 1, exact for c < 2^18 and 2 <= W <= 2^13 (the product
 // exceeds 2^32 c / W by less than c, which moves c / W by less than 2^-14,
-// below the gap 1 / W to the next integer).  W = 1 only with n = 1 (the
-// grid has one block per 64 tokens at most), where the multiplier wraps to
+// below the gap 1 / W to the next integer).  W = 1 only with n = 1 (a
+// grid has one block per 16 tokens at most), where the multiplier wraps to
 // 0 and column 0's block is 0.
 __device__ __forceinline__ int block_of(const IncDev& a, int c) { return int(__umulhi(unsigned(c), a.w_magic)); }
 inline unsigned int w_magic_of(int W) { return unsigned(0xffffffffu / unsigned(W)) + 1u; }
@@ -254,21 +254,6 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x)
   else
     lm = wave_max_u32(hi == hm ? unsigned(x) : 0u);
   return ((unsigned long long)hm << 32) | lm;
-}
-
-__device__ __forceinline__ long long wave_max_i64(long long x) {
-  long long y;
-  y = (long long)dpp_u64<kDppSteps[0]>((unsigned long long)x); x = y > x ? y : x;
-  y = (long long)dpp_u64<kDppSteps[1]>((unsigned long long)x); x = y > x ? y : x;
-  y = (long long)dpp_u64<kDppSteps[2]>((unsigned long long)x); x = y > x ? y : x;
-  y = (long long)dpp_u64<kDppSteps[3]>((unsigned long long)x); x = y > x ? y : x;
-  long long m = (long long)lane_u64((unsigned long long)x, 0);
-#pragma unroll
-  for (int r = 16; r < 64; r += 16) {
-    y = (long long)lane_u64((unsigned long long)x, r);
-    m = y > m ? y : m;
-  }
-  return m;
 }
 
 __device__ __forceinline__ long long wave_sum_i64(long long x) {

@@ -48,3 +48,39 @@ def test_scores_from_the_spatial_order(kind, n, nn):
     # float64 sums of float64 terms in another order.
     assert np.allclose(r.cpu().numpy(), ref["r"], rtol=1e-12, atol=1e-15)
     assert np.allclose(v.cpu().numpy(), ref["v"], rtol=2 ** -23, atol=0.0)
+
+
+def _strange(kind, n, rng):
+    p = rng.random((n, 3)) * [10, 10, 3]
+    some = rng.choice(n, 40, replace=False)
+    if kind == "nan":
+        p[some, rng.integers(0, 3, 40)] = np.nan
+    elif kind == "infinite":
+        p[some, rng.integers(0, 3, 40)] = np.where(rng.random(40) < 0.5, np.inf, -np.inf)
+    elif kind == "all nan":
+        p[:] = np.nan
+    elif kind == "huge":
+        p[some] = rng.choice([-3.0e38, 3.0e38], (40, 3))
+    else:                                        # "tiny": differences below the normal range
+        p *= 1e-42
+    return p.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["nan", "infinite", "all nan", "huge", "tiny"])
+@pytest.mark.parametrize("n,nn", [(1024, 16), (1091, 127), (2500, 3)])
+def test_strange_positions_as_in_index_order(kind, n, nn):
+    # The spatial order only leaves tokens out, so whatever a distance is, the
+    # tables are those of the index order (a workspace without room for it).
+    import paper_2608_13226_amd as cp
+    from tests.test_gpu_workspaces import up
+    rng = np.random.default_rng(n + nn)
+    pos = torch.from_numpy(_strange(kind, n, rng)).cuda()
+    feats = torch.from_numpy(rng.normal(0, 1, (n, 16)).astype(np.float32)).cuda()
+    frame = torch.from_numpy(rng.integers(0, 9, n).astype(np.int32)).cuda()
+    least = up(n * (nn + 1) * 4) + up(n * nn * 24) + 256 + up(n * 8) + up((n + 255) // 256 * 8)
+    print(f"capacity sorted {kind} n={n} nn={nn}", flush=True)
+    v0, r0 = cp.fst_capacity(feats, pos, frame, nn)
+    v1, r1 = cp.fst_capacity(feats, pos, frame, nn, workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert torch.equal(r0.view(torch.int64), r1.view(torch.int64))
+    assert torch.equal(v0.view(torch.int32), v1.view(torch.int32))

@@ -187,9 +187,8 @@ cp_status coverprune_fst_capacity(const void* feats, cp_dtype dtype, int64_t n, 
  *             asked for) n 2^36 units of that form's grid, which bounds the
  *             error of its sums to 2^-30 and 2^-36, and no gains that only
  *             differ below 2^-31 met in a comparison.  Otherwise, for k = n,
- *             for a few picks of a small scene (k <= 12, n <= 2048), or with
- *             a workspace for the sweeps alone, the whole matrix is read
- *             each step.
+ *             for a few picks (7 to 22, by n), or with a workspace for the
+ *             sweeps alone, the whole matrix is read each step.
  *             CP_SGS_INCREMENTAL: the gains are summed once at b = c0 and then
  *             updated, step by step, from the rows of the targets whose best
  *             cost the pick lowers (their old and new b); the terms are the

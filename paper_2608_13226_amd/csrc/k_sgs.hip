@@ -452,6 +452,17 @@ hipError_t max_coresident(int& blocks) {
 // from megabytes past 256 MB; the sweeps' is 2 MB at n = 4096, 9 MB at 16384.
 constexpr int kFastN = 8192;
 
+// Picks up to which the sweeps alone are as fast.  A sweep reads rows that
+// are not a multiple of 16 bytes by single floats and takes twice as long; beyond
+// 4096 tokens the cost leaves the Infinity Cache bit by bit.  us of sweeps and
+// of the incremental form: 12 of 1024: 175, 191; 12 of 2048: 268, 265; 18 of
+// 3000: 497, 528; 20 of 4096: 565, 596; 16 of 6272: 676, 703; 8 of 8192: 566,
+// 679; 12 of 8192: 832, 759; 8 of 2049: 371, 339; 8 of 5070: 486, 492.
+int sweeps_k(int n) {
+  if (n % 4 != 0) return 7;
+  return n <= 2048 ? 12 : n <= 3500 ? 19 : n <= 5000 ? 22 : n <= 7000 ? 16 : 10;
+}
+
 size_t sgs_sweep_workspace_bytes(int64_t n, int64_t k) { return layout(n, k).total; }
 
 size_t sgs_workspace_bytes(int64_t n, int64_t k) {
@@ -460,10 +471,11 @@ size_t sgs_workspace_bytes(int64_t n, int64_t k) {
 
 hipError_t launch_sgs_dense(const SgsParams& p, hipStream_t stream) {
   // With every token picked the objective is only what tokens cost themselves,
-  // mostly nothing, and the sweeps would have to follow.
+  // mostly nothing, and the sweeps would have to follow.  A few picks do not
+  // pay for the incremental form's first pass and launches.
   SgsChecked checked{};
   const double* last_gain = nullptr;
-  if (p.n <= kFastN && p.k < p.n && p.c0 > 0.f && p.workspace_bytes >= sgs_workspace_bytes(p.n, p.k)) {
+  if (p.n <= kFastN && p.k > sweeps_k(p.n) && p.k < p.n && p.c0 > 0.f && p.workspace_bytes >= sgs_workspace_bytes(p.n, p.k)) {
     const Layout L = layout(p.n, p.k);
     SgsParams q = p;
     q.workspace = static_cast<char*>(p.workspace) + L.total;

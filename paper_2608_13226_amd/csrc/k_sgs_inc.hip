@@ -2075,20 +2075,17 @@ bool use_rows(int64_t n, int W) { return n <= kRowsMaxN && W <= kRowsMaxW; }
 // launch whatever the schedule asked for: the rows form spends some 0.1 ms on
 // its launches and first steps before its steps get cheaper than the exchange
 // form's 5 to 7 us (k = 12 of 256 tokens: 115 against 160 us, 30 of 300: 210
-// against 185, 51 of 1024: 390 against 292).  Same result.  With the data
-// checked for the dense form the sweeps are the alternative, and as fast up
-// to kCheckedShortK picks (10 of 1024: 153 us of sweeps, 178 of the rows
-// form; 12 of 256: 139, 144; 12 of 2048: 268, 265; 16 of 2048: 329, 297).
+// against 185, 51 of 1024: 390 against 292).  Same result.
 // Blocks of a scene's greedy, and whether it is the rows form.  The rows form
 // takes one block per kRowsPer tokens (up to one per compute unit: the early
 // steps and the hits' row segments spread over more of the chip, 4096 tokens
 // 0.05 ms faster than with one per 32), the exchange form one per 64.
 constexpr int kRowsPer = 16;
-constexpr int kShortN = 2048, kShortK = 20, kCheckedShortK = 12;
-bool short_greedy(int64_t n, int64_t k, int64_t short_k = kShortK) { return n <= kShortN && k <= short_k; }
-int inc_blocks(int64_t n, int64_t k, int cus, bool compact, bool* rows, int64_t short_k = kShortK) {
+constexpr int kShortN = 2048, kShortK = 20;
+bool short_greedy(int64_t n, int64_t k) { return n <= kShortN && k <= kShortK; }
+int inc_blocks(int64_t n, int cus, bool exchange, bool* rows) {
   const int nb = blocks_for(n, cus, kRowsPer);
-  *rows = !compact && !short_greedy(n, k, short_k) && use_rows(n, cols_for(n, nb));
+  *rows = !exchange && use_rows(n, cols_for(n, nb));
   return *rows ? nb : blocks_for(n, cus, 64);
 }
 
@@ -2264,7 +2261,7 @@ hipError_t run_incremental(const SgsParams& p, bool compact, const SgsFused* fus
   hipError_t e = hipError_t(device_cus(&cus));
   if (e != hipSuccess) return e;
   bool rows = false;
-  const int nb = inc_blocks(p.n, p.k, cus, compact, &rows, checked ? kCheckedShortK : kShortK);
+  const int nb = inc_blocks(p.n, cus, compact || (!checked && short_greedy(p.n, p.k)), &rows);
   const int W = cols_for(p.n, nb);
   // note_tie covers the exchange of the rows form with one column group.
   if (checked && (!rows || W > 64)) return hipSuccess;

@@ -32,6 +32,18 @@ def _equal(a, b):
                                               (a.objective, b.objective), (a.assign, b.assign)))
 
 
+# Few picks do not pay for the incremental form: the line depends on n.
+@pytest.mark.parametrize("n,last", [(1000, 12), (1001, 7), (2049, 7), (3000, 19), (4096, 22), (6000, 16), (8192, 10)])
+def test_few_picks_take_the_sweeps_alone(n, last):
+    import paper_2608_13226_amd as cp
+    cost, cap = _cost(n, n)
+    for k in (last, last + 1):
+        print(f"sgs dense guard few picks n={n} k={k}", flush=True)
+        full, ref = cp.sgs_select(cost, cap, k, c0=3.0, check=True), _sweeps(cost, cap, k, 3.0)
+        assert torch.equal(full.selected, ref.selected)
+        assert _equal(full, ref) == (k == last)
+
+
 # 2500 tokens and more: the early kernel, whose launches the check also covers.
 @pytest.mark.parametrize("n,k", [(300, 40), (2049, 21), (2500, 60), (8192, 40)])
 def test_ordinary_data_keep_the_incremental_result(n, k):

@@ -2030,7 +2030,6 @@ __global__ __launch_bounds__(kPassThreads) void inc_first_pass_kernel(IncDev a, 
 // with its own slots, change lists and abort flag, so the scenes' greedies
 // proceed independently side by side.
 constexpr int kMaxBatch = 16;
-constexpr int kBatchListK = 32;                       // batches of no more picks do without the list kernel
 
 struct IncBatch {
   int count;
@@ -2389,15 +2388,26 @@ hipError_t launch_sgs_incremental_batch(const SgsParams* p, int count, bool comp
   if (count > cus) return hipErrorInvalidValue;
   bool rows = false;
   for (int s = 0; s < count; ++s) rows = rows || (!compact && !short_greedy(p[s].n, p[s].k));
+  // Where some block has more than 64 columns the units ran out before any
+  // scene reached its cap, so both shares are the same and every block is a
+  // whole group, as the kernels for such blocks and the exchange form need.
   int nb[kMaxBatch], nb64[kMaxBatch];
   const int used = share_blocks(p, count, cus, rows ? kRowsPer : 64, nb);
   share_blocks(p, count, cus, 64, nb64);
   // The rows form when every scene allows it (one form per launch) and one is
   // not short, with the early and list kernels for the scenes they serve.
-  // A handful of picks does not pay for two more launches (three scenes of 256
-  // tokens, K = 25: 221 us with the list kernel).
-  bool early = false, lists = false;
-  for (int s = 0; s < count; ++s) lists = lists || (rows && p[s].k > kBatchListK);
+  // The list kernel serves when the scene with the most work (n k) has enough
+  // steps left from its lists on to pay for two more launches, the scenes' builds, (beyond
+  // kEarlyMinN) the early kernel, and, with more than 100 columns a block, pairs
+  // that do not fit in LDS.  us without and with it: two scenes of 1000 tokens,
+  // K = 50 373, 324; eight, K = 50 521, 540; four of 2000, K = 40 504, 548;
+  // K = 60 608, 587; four of 6000, K = 100 1950, 1963; sixteen of 2000 (125
+  // columns), K = 80 1311, 1412; eight of 4000, K = 80 1530, 1875.
+  int big = 0;
+  for (int s = 1; s < count; ++s)
+    if (int64_t(p[s].n) * p[s].k > int64_t(p[big].n) * p[big].k) big = s;
+  const int least = cols_for(p[big].n, nb[big]) > 100 ? 100 : p[big].n > kEarlyMinN ? 56 : 32 + 2 * count;
+  bool early = false, lists = rows && p[big].k - list_step(p[big].n) > least;
   int wmax = 0, nmax = 0;
   for (int s = 0; s < count; ++s) {
     const int W = cols_for(p[s].n, nb[s]);

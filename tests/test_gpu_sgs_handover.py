@@ -10,7 +10,7 @@ import pytest
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-N, K, FIRST = 2304, 60, 18
+N, K, FIRST = 2304, 90, 18
 
 
 def _scene(dense_steps, seed):

@@ -86,3 +86,33 @@ def test_near_ties_in_the_local_greedy():
     print("sgs order local", flush=True)
     r = cp.sgs_local_select(cost, cap, torch.from_numpy(nbr.astype(np.int32)).cuda(), pairs, c0=3.0, check=True)
     assert r.selected.tolist() == want
+
+
+def batch_widths(sizes, units=256):
+    """Tokens per group of each scene of a batch: every scene has one block, then the one with the most tokens
+    a block gains one (up to one per 64 tokens) until the compute units run out."""
+    nb = [1] * len(sizes)
+    for _ in range(units - len(sizes)):
+        wide = [-(-n // b) if b < -(-n // 64) else 0 for n, b in zip(sizes, nb)]
+        if max(wide) == 0:
+            break
+        nb[wide.index(max(wide))] += 1
+    return [-(-n // b) for n, b in zip(sizes, nb)]
+
+
+def test_near_ties_of_a_small_scene_beside_large_ones():
+    # The large scenes get blocks of more than 64 columns, and one kernel serves
+    # all of the batch: the small one's groups hold there too.
+    import paper_2608_13226_amd as cp
+    n, pairs = 300, 30
+    width = batch_widths([6000] * 4 + [n])[-1]
+    assert width > 64
+    c, v, want = scene(n, pairs, 0, 0, 0, width, 300)
+    cost, cap = _cuda(c, v)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    big = [3.0 * torch.rand(6000, 6000, device="cuda", generator=g) for _ in range(4)]
+    caps = [torch.rand(6000, device="cuda", generator=g) for _ in range(4)]
+    for k in (20, 100):                                     # without and with the list kernel
+        print(f"sgs order mixed batch k={k}", flush=True)
+        r = cp.sgs_select_batch(big + [cost], caps + [cap], [k] * 4 + [pairs], c0=3.0, check=True)
+        assert r[-1].selected.tolist() == want

@@ -98,7 +98,7 @@ __device__ __forceinline__ void inc_body(const IncDev& a, int blk, int nb) {
     if (tid < kWaves) sLw[tid] = tid == 0 ? L0 : 0;
   }
 
-  publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), su);
+  publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), su);
 
   for (int step = 0; step < a.k; ++step) {
     // Some block has a candidate while unchosen columns remain; the clamp
@@ -264,7 +264,7 @@ __device__ __forceinline__ void inc_body(const IncDev& a, int blk, int nb) {
 
     // 4. This block's candidate for the next step.
     if (step + 1 < a.k)
-      publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, (step + 1) & 1, blk),
+      publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, (step + 1) & 1, blk),
                      epoch_of(step + 1), su);
   }
   __syncthreads();
@@ -477,7 +477,7 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
     if (kSpec)
       publish_rows<true>(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0));
     else
-      publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), su);
+      publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, 0, blk), epoch_of(0), su);
   }
 
   const int nch = a.ldt / kRowChunk;
@@ -776,7 +776,7 @@ __device__ __forceinline__ void rows_body(const IncDev& a, int blk, int nb) {
       if (kSpec)
         publish_rows<true>(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc));
       else
-        publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc), su);
+        publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, xc & 1, blk), epoch_of(xc), su);
     }
     predicted = next;
     tpred = rn;
@@ -892,7 +892,7 @@ __device__ __forceinline__ void early_body(const IncDev& a, int blk, int nb) {
     if (NG == 1)
       publish_rows<true>(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x));
     else
-      publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x), su);
+      publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x), su);
   };
   publish(0);
 

@@ -47,6 +47,17 @@ constexpr int kLocalMaxG = 128;
 constexpr int kChunkT = 256;                          // targets per wave-load of the winner's row
 constexpr int kLoadsT = kLocalMaxN / kChunkT / kWaves;  // such loads per wave and step
 constexpr int kLocalChain = 5;                        // predicted steps in a row at most
+// A chain whose first candidate fails costs 1 to 1.5 us, and the first picks
+// change the order each time: after m failures in a row m - 1 exchanges
+// (kLocalRest at most) go without a chain, and a greedy starts as after
+// kLocalFails.
+constexpr int kLocalRest = 7, kLocalFails = 5;
+// Whether a greedy uses chains at all (one column per lane): short ones end
+// before the order settles, and few blocks make short chains.  us without and
+// with them, g = 64: 37 picks of 300 tokens 173, 194; 50 of 1000 236, 260; 75 of
+// 1500 344, 345; 100 of 2000 448, 417 (g = 16: 388, 402); 20 of 8192 303, 315;
+// 100 of 8192 738, 722.
+bool chains_for(int n, int k, int W) { return W <= 64 && n > 600 && k > (n < 8000 ? 100 : 40); }
 constexpr int kBandPer = kLocalMaxG / 64;             // a chain candidate's neighbours in a lane
 constexpr int kTile = 64;                             // transposing kernel's tile
 
@@ -80,6 +91,7 @@ struct LocalDev {
   int* scale;          // the fixed-point exponent S, for the objective sums
 };
 
+template <bool SPEC>
 __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
   const IncDev& a = L.a;
   const int g = L.g;
@@ -104,7 +116,7 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
   __shared__ unsigned long long su[kWaves];
   __shared__ int sflag[2];
   __shared__ long long sLw[kWaves];            // this block's objective part, one running share per wave
-  __shared__ unsigned long long sk1[kMaxBlocks], sk2[kMaxBlocks];   // the last exchange's keys
+  __shared__ unsigned long long sk1[SPEC ? kMaxBlocks : 1], sk2[SPEC ? kMaxBlocks : 1];   // the last exchange's keys
   __shared__ long long sgr;                    // the next chain candidate's gain
 
   for (int j = tid; j < a.ldt; j += kBlock) sball[j] = j < a.n ? a.c0 : -__builtin_inff();
@@ -202,13 +214,11 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
     }
   };
 
-  // Prediction needs one column per lane (any device with 256 compute units).
-  const bool spec = a.W <= 64;
   auto publish = [&](int x) {
-    if (spec)
+    if (SPEC)
       publish_rows<false>(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x));
     else
-      publish_argmax(a, sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x), su);
+      publish_argmax(sG, ssel, lo, cnt, S, cand_slot(a.cand, x & 1, blk), epoch_of(x), su);
   };
   __syncthreads();
   local_gains();
@@ -218,6 +228,8 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
   int xc = 0;                  // exchanges so far
   int pos = 0;                 // the step's place in the chain (0: after an exchange)
   bool predicted = false;
+  bool chain = false;          // the last exchange's chain is followed
+  int fails = kLocalFails, rest = kLocalFails - 1;
   long long gpred = 0;         // a predicted winner's gain
   int rc[kLocalChain + 1];     // the chain (-1 past its end) and the truncated gains it must exceed
   unsigned long long ub[kLocalChain + 1];
@@ -238,12 +250,14 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
     int t = -1;
     if (!predicted) {
       const unsigned long long* slots = cand_slot(a.cand, xc & 1, 0);
-      const int tw = spec ? read_winner_rows<false>(a, slots, epoch_of(xc), nb, su, sflag, sk1, sk2, nullptr)
+      const int tw = SPEC ? read_winner_rows<false>(a, slots, epoch_of(xc), nb, su, sflag, sk1, sk2, nullptr)
                           : read_winner(slots, epoch_of(xc), nb, a.abort, a.poll_limit, su, sflag);
       ++xc;
       if (tw < 0) break;
       t = min(tw, a.n - 1);
       pos = 0;
+      chain = SPEC && rest == 0;
+      rest -= rest > 0 ? 1 : 0;
     } else {
 #pragma unroll
       for (int m = 1; m <= kLocalChain; ++m)
@@ -263,7 +277,7 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
 #pragma unroll
     for (int i = 0; i < kLoadsT; ++i)
       if (w + i * kWaves < nch) xr[i] = predicted ? xr2[i] : row[(w + i * kWaves) * (kChunkT / 4) + lane];
-    if (spec && !predicted) {
+    if (chain && !predicted) {
       // The chain, the same in every wave, while the row is in flight; then
       // wave m loads r_m's band.
       const int bt = block_of(a, t);
@@ -346,7 +360,7 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
         rn = rc[m];
         un = ub[m];
       }
-    if (!spec || step + 1 >= a.k) rn = -1;
+    if (!chain || step + 1 >= a.k) rn = -1;
     if (rn >= 0) {
       const f32x4* rowr = reinterpret_cast<const f32x4*>(a.T + size_t(rn) * a.ldt);
 #pragma unroll
@@ -382,6 +396,10 @@ __global__ __launch_bounds__(kBlock) void sgs_local_kernel(LocalDev L) {
     if (step + 1 < a.k && !next) {
       local_gains();
       publish(xc);
+    }
+    if (chain && pos == 0) {
+      fails = next ? 0 : fails + 1;
+      rest = next ? 0 : min(fails - 1, kLocalRest);
     }
     predicted = next;
     pos += next ? 1 : 0;
@@ -425,13 +443,11 @@ hipError_t launch_sgs_local(const SgsParams& p, const int32_t* nbr, int g, hipSt
   const int W = (p.n + nb - 1) / nb;
   const int ldt = local_ldt(p.n);
   const size_t lds = size_t((W + 1) & ~1) * 8 + size_t(ldt) * 4 + size_t(W) * g * (4 + 4 + 2) + size_t(W) * (4 + 1) + 16;
-  if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(sgs_local_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds))) != hipSuccess)
-    return e;
+  const void* kernel = chains_for(p.n, p.k, W) ? reinterpret_cast<const void*>(sgs_local_kernel<true>)
+                                               : reinterpret_cast<const void*>(sgs_local_kernel<false>);
+  if ((e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds))) != hipSuccess) return e;
   int per_cu = 0;
-  if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(sgs_local_kernel),
-                                                        kBlock, lds)) != hipSuccess)
-    return e;
+  if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, lds)) != hipSuccess) return e;
   if (per_cu < 1) return hipErrorCooperativeLaunchTooLarge;
 
   const Layout X = layout(p.n, p.k);
@@ -472,9 +488,7 @@ hipError_t launch_sgs_local(const SgsParams& p, const int32_t* nbr, int g, hipSt
   transpose_kernel<<<dim3(tiles, tiles), 256, 0, stream>>>(p.cost, p.n, a.T, ldt);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   void* args[] = {&d};
-  if ((e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(sgs_local_kernel), dim3(nb), dim3(kBlock), args,
-                                      lds, stream)) != hipSuccess)
-    return e;
+  if ((e = hipLaunchCooperativeKernel(kernel, dim3(nb), dim3(kBlock), args, lds, stream)) != hipSuccess) return e;
   if ((e = launch_mark_aborted(a.abort, a.selected, a.k, stream)) != hipSuccess) return e;
   if (p.step_objective) {
     local_objective_kernel<<<(p.k + 255) / 256, 256, 0, stream>>>(d.part, nb, p.k, d.scale, p.step_objective);

@@ -179,13 +179,8 @@ __device__ __forceinline__ unsigned long long epoch_of(int step) {
 
 __global__ void sgs_inc_init_kernel(IncDev a) {
   const int gt = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
-  for (int s = gt; s < kMaxBlocks; s += nt) {
-    a.lens[size_t(s) * kSlotStride] = 0ull;
-    for (int w = 0; w < kSlotStride; ++w) {
-      a.cand[size_t(s) * kSlotStride + w] = 0ull;
-      a.cand[size_t(kMaxBlocks + s) * kSlotStride + w] = 0ull;
-    }
-  }
+  for (int s = gt; s < kMaxBlocks; s += nt) a.lens[size_t(s) * kSlotStride] = 0ull;
+  for (int i = gt; i < 2 * kMaxBlocks * kSlotStride; i += nt) a.cand[i] = 0ull;
   for (int j = gt; j < a.n; j += nt)
     if (a.assign) a.assign[j] = -1;
   if (gt == 0) *a.abort = a.abort_init & 1u;
@@ -401,8 +396,8 @@ __device__ __forceinline__ int first_of(unsigned long long tie, int group, long 
 // its candidate for the step.  With at most 64 columns wave 0 does it alone,
 // one column per lane, and no barrier follows: the callers' next step begins
 // with one (read_winner), and the gains and chosen flags it reads were last
-// written by wave 0 itself.  More columns form one group with the others of
-// their block, so the exact gains decide.
+// written by wave 0 itself.  A block is one group here, so the exact gains
+// decide.
 __device__ __forceinline__ unsigned long long column_key(const long long* sG, const unsigned char* ssel, int lo, int i,
                                                          int cnt, int S) {
   return i < cnt && !ssel[i] ? pack_key(fx_to_double(sG[i], S), lo + i) : kNoCandidate;
@@ -430,13 +425,16 @@ __device__ __forceinline__ WaveBest wave_best(const IncDev& a, const long long* 
   }
   return r;
 }
-__device__ __forceinline__ void publish_argmax(const IncDev& a, const long long* sG, const unsigned char* ssel, int lo,
+__device__ __forceinline__ void publish_argmax(const long long* sG, const unsigned char* ssel, int lo,
                                                int cnt, int S, unsigned long long* slot, unsigned long long epoch,
                                                unsigned long long* su) {
   if (cnt <= 64) {
     if (threadIdx.x >= 64) return;
-    const WaveBest best = wave_best(a, sG, column_key(sG, ssel, lo, threadIdx.x, cnt, S), lo);
-    if (threadIdx.x == 0) put(slot, best.key | epoch);
+    const int i = threadIdx.x;
+    const unsigned long long g1 = i < cnt && !ssel[i] ? (unsigned long long)sG[i] + 1ull : 0ull;   // 0: no candidate
+    const unsigned long long top = wave_max_u64(g1);
+    const int first = __builtin_ctzll(__ballot(g1 == top));
+    if (i == 0) put(slot, (top ? pack_key(fx_to_double((long long)(top - 1), S), lo + first) : kNoCandidate) | epoch);
     return;
   }
   __shared__ int si[kWaves];

@@ -197,6 +197,15 @@ def test_local_with_all_targets_is_the_dense_greedy():
     assert np.array_equal(a[3], r.assign.cpu().numpy())
 
 
+@pytest.mark.parametrize("n,k", [(600, 150), (601, 150), (700, 100), (700, 101), (1500, 200)])
+def test_local_without_and_with_chains(n, k):
+    # Short greedies and small scenes exchange candidates every step, others
+    # follow chains of predicted winners.
+    s = _sub("n4096_d1152", n, 3)
+    print(f"sgs local chains n={n} k={k}", flush=True)
+    _local_case(s, k, 24)
+
+
 def test_local_arbitrary_table():
     # Any table of distinct targets, not only nearest neighbours.
     s = _sub("n4096_d1152", 500, 16)

@@ -74,9 +74,11 @@ def test_near_ties_inside_and_across_groups(n, pairs, idle, early, long):
         assert r.selected.tolist() == want
 
 
-def test_near_ties_in_the_local_greedy():
+# Without and with chains of predicted winners.
+@pytest.mark.parametrize("pairs", [60, 120])
+def test_near_ties_in_the_local_greedy(pairs):
     import paper_2608_13226_amd as cp
-    n, pairs = 2400, 60
+    n = 2400
     c, v, want = scene(n, pairs, 0, 0, 0, group_width(n), 3)
     nbr = np.repeat(np.arange(n)[:, None], 4, axis=1)       # cost 3.0 to oneself: no gain
     for i in range(n):

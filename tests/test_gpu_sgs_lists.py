@@ -86,3 +86,30 @@ def test_rounds_in_a_batch_with_wide_blocks():
         one = cp.sgs_select(c, v, k, c0=3.0, incremental=True, compact=True, check=True)
         for x, y in zip((r.selected, r.gain, r.objective, r.assign), (one.selected, one.gain, one.objective, one.assign)):
             assert torch.equal(x, y)
+
+
+# Picks past the last gain, four a round: targets without capacity still change
+# hands, in the order of the picks.
+@pytest.mark.parametrize("kind", ["constant", "few targets", "few groups"])
+@pytest.mark.parametrize("n,k", [(300, 129), (300, 300), (1001, 500), (2500, 250), (5070, 700)])
+def test_picks_of_no_gain(n, k, kind):
+    import paper_2608_13226_amd as cp
+    rng = np.random.default_rng(n + k)
+    v = rng.random(n).astype(np.float32)
+    if kind == "constant":
+        c = np.full((n, n), 1.5, np.float32)
+    elif kind == "few targets":
+        c = (3.0 * rng.random((n, n))).astype(np.float32)
+        v[rng.permutation(n)[40:]] = 0.0
+    else:
+        at = rng.integers(0, 30, n)
+        c = (3.0 * rng.random((30, 30))).astype(np.float32)[at][:, at]
+    if kind != "constant":
+        np.fill_diagonal(c, 0.0)
+    cost, cap = torch.from_numpy(c).cuda().t().contiguous(), torch.from_numpy(v / v.sum()).cuda()
+    print(f"sgs lists no gain {kind} n={n} k={k}", flush=True)
+    one = cp.sgs_select(cost, cap, k, c0=3.0, incremental=True, compact=True, check=True)
+    assert kind == "few groups" or float(one.gain[-1]) == 0.0
+    r = cp.sgs_select(cost, cap, k, c0=3.0, incremental=True, check=True)
+    for x, y in zip((r.selected, r.gain, r.objective, r.assign), (one.selected, one.gain, one.objective, one.assign)):
+        assert torch.equal(x, y)

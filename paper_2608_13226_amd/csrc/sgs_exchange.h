@@ -500,14 +500,22 @@ template <bool SPANS>
 __device__ __forceinline__ void publish_rows(const IncDev& a, const long long* sG, const unsigned char* ssel, int lo,
                                              int cnt, int S, unsigned long long* slot, unsigned long long epoch) {
   if (threadIdx.x >= 64) return;
+  if (!SPANS) {
+    // The block is a group: its first column by exact gain, as in publish_argmax.
+    const int i = threadIdx.x;
+    const unsigned long long g1 = i < cnt && !ssel[i] ? (unsigned long long)sG[i] + 1ull : 0ull;
+    const unsigned long long key = g1 ? pack_key(fx_to_double((long long)(g1 - 1), S), lo + i) : kNoCandidate;
+    const int first = __builtin_ctzll(__ballot(g1 == wave_max_u64(g1)));
+    const unsigned long long second = wave_max_u64(i == first ? kNoCandidate : key);
+    if (i < 2) put(slot + i, (i ? second : lane_u64(key, first)) | epoch);
+    return;
+  }
   const WaveBest best = wave_best(a, sG, column_key(sG, ssel, lo, threadIdx.x, cnt, S), lo);
   unsigned long long word = threadIdx.x ? best.second : best.key;
-  if (SPANS) {
-    // One store of three lanes; without a candidate the gain is not read.
-    const unsigned long long g = lane_u64((unsigned long long)sG[int(threadIdx.x) < cnt ? threadIdx.x : 0], best.lane);
-    if (threadIdx.x == 2) word = g & ~kEpoch;
-  }
-  if (threadIdx.x < (SPANS ? 3 : 2)) put(slot + threadIdx.x, word | epoch);
+  // One store of three lanes; without a candidate the gain is not read.
+  const unsigned long long g = lane_u64((unsigned long long)sG[int(threadIdx.x) < cnt ? threadIdx.x : 0], best.lane);
+  if (threadIdx.x == 2) word = g & ~kEpoch;
+  if (threadIdx.x < 3) put(slot + threadIdx.x, word | epoch);
 }
 
 // Of the blocks' best candidates with the truncated gain of m (the one with

@@ -152,3 +152,19 @@ def test_without_gains_and_objectives():
         assert st == 0
         torch.cuda.synchronize()
         assert torch.equal(sel, _sweeps(cost, cap, k, c0).selected)
+
+
+@pytest.mark.parametrize("n,k", [(600, 100), (3000, 120)])
+def test_smooth_gains(n, k):
+    # Neighbours on a line have nearly equal gains: whether a pick among them
+    # is the sweeps' is seen, so the result is theirs either way.
+    import paper_2608_13226_amd as cp
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.rand(n, 1, device="cuda", generator=g)
+    cost = (3.0 * (x - x.t()).abs()).contiguous()
+    cap = torch.full((n,), 1.0 / n, device="cuda")
+    print(f"sgs dense guard line n={n}", flush=True)
+    full, ref = cp.sgs_select(cost, cap, k, c0=3.0, check=True), _sweeps(cost, cap, k, 3.0)
+    assert torch.equal(full.selected, ref.selected) and torch.equal(full.assign, ref.assign)
+    assert torch.allclose(full.gain, ref.gain, rtol=2.0 ** -30, atol=0.0)
+    assert torch.allclose(full.objective, ref.objective, rtol=2.0 ** -36, atol=0.0)
